@@ -427,7 +427,7 @@ __device__ __forceinline__ void rowstats_body(const LayerArgs& a, const SeqArgs&
 }
 
 template <int DT, int D>
-__device__ __forceinline__ void rowstats_block(const LayerArgs& a, const int b) {
+__device__ __forceinline__ void rowstats_block(const LayerArgs& a, const int b, const uint32_t touched) {
   using S = Stager<DT, D, stage_bytes<DT, D>()>;
   constexpr int NS = 4;  // 4-slot ring
   __shared__ uint4 slot0[S::VEC];
@@ -440,6 +440,7 @@ __device__ __forceinline__ void rowstats_block(const LayerArgs& a, const int b) 
   const SeqArgs& sq = a.seq[find_seq(a, b, [](const SeqArgs& t) { return t.blk_kpass; })];
   int g, j, u, p, P;
   kpass_locate(a, sq, b - sq.blk_kpass, g, j, u, p, P);
+  args_ready(touched);
   const int cnt = a.grp_off[g + 1] - a.grp_off[g];
   const int sel0 = a.grp_off[g] + j * a.hpr;
   const int n_sel = j < group_units(cnt, a.hpr) && cnt > 0 ? unit_heads(cnt, a.hpr, j) : 0;
@@ -468,7 +469,7 @@ __device__ __forceinline__ void rowstats_block(const LayerArgs& a, const int b) 
 
 template <int DT, int D>
 __global__ __launch_bounds__(kKpThreads) __attribute__((amdgpu_waves_per_eu(2))) void rowstats_kernel(const LayerArgs a) {
-  rowstats_block<DT, D>(a, blockIdx.x);
+  rowstats_block<DT, D>(a, blockIdx.x, args_touch<sizeof(LayerArgs)>());
 }
 
 // The layer of workgroup b of a multi-layer K-pass launch.
@@ -485,8 +486,9 @@ __device__ __forceinline__ int layer_of(const LayersArgs& m, int b) {
 // all.
 template <int DT, int D>
 __global__ __launch_bounds__(kKpThreads) __attribute__((amdgpu_waves_per_eu(2))) void rowstats_layers_kernel(const LayersArgs m) {
+  const uint32_t touched = args_touch<sizeof(LayersArgs)>();
   const int l = layer_of(m, blockIdx.x);
-  rowstats_block<DT, D>(m.lay[l], blockIdx.x - m.blk[l]);
+  rowstats_block<DT, D>(m.lay[l], blockIdx.x - m.blk[l], touched);
 }
 
 // Online merge of (max logit, sum of exp2) pairs in exp2 units.
@@ -710,7 +712,7 @@ __device__ __forceinline__ void score_body(const LayerArgs& a, const SeqArgs& sq
 }
 
 template <int DT, int D>
-__device__ __forceinline__ void score_block(const LayerArgs& a, const int b) {
+__device__ __forceinline__ void score_block(const LayerArgs& a, const int b, const uint32_t touched) {
   using S = Stager<DT, D, stage_bytes<DT, D>()>;
   constexpr int NS = 4;  // 4-slot ring
   __shared__ uint4 slot0[S::VEC];
@@ -734,6 +736,7 @@ __device__ __forceinline__ void score_block(const LayerArgs& a, const int b) {
   }
   int g, j, u, p, P;
   kpass_locate(a, sq, b - sq.blk_kpass, g, j, u, p, P);
+  args_ready(touched);
   const int cnt = a.grp_off[g + 1] - a.grp_off[g];
   const int sel0 = a.grp_off[g] + j * a.hpr;
   const int n_sel = j < group_units(cnt, a.hpr) && cnt > 0 ? unit_heads(cnt, a.hpr, j) : 0;
@@ -769,14 +772,15 @@ __device__ __forceinline__ void score_block(const LayerArgs& a, const int b) {
 
 template <int DT, int D>
 __global__ __launch_bounds__(kKpThreads) __attribute__((amdgpu_waves_per_eu(2))) void score_kernel(const LayerArgs a) {
-  score_block<DT, D>(a, blockIdx.x);
+  score_block<DT, D>(a, blockIdx.x, args_touch<sizeof(LayerArgs)>());
 }
 
 // The window-sum passes of up to kLayersPerLaunch layers in one launch.
 template <int DT, int D>
 __global__ __launch_bounds__(kKpThreads) __attribute__((amdgpu_waves_per_eu(2))) void score_layers_kernel(const LayersArgs m) {
+  const uint32_t touched = args_touch<sizeof(LayersArgs)>();
   const int l = layer_of(m, blockIdx.x);
-  score_block<DT, D>(m.lay[l], blockIdx.x - m.blk[l]);
+  score_block<DT, D>(m.lay[l], blockIdx.x - m.blk[l], touched);
 }
 
 // ---------------------------------------------------------------------------
@@ -987,7 +991,10 @@ __device__ __forceinline__ void pool_body(const LayerArgs& a, int b) {
 // only its own halo in registers, and the common small radii run at full
 // occupancy.
 template <int R>
-__global__ __launch_bounds__(kThreads) void pool_kernel(const LayerArgs a) { pool_body<R>(a, blockIdx.x); }
+__global__ __launch_bounds__(kThreads) void pool_kernel(const LayerArgs a) {
+  args_ready(args_touch<sizeof(LayerArgs)>());
+  pool_body<R>(a, blockIdx.x);
+}
 
 // Pooling, head mean, scores and the first-level histogram of several layers
 // at once (ckv_compress_stack): layer l's argument block is read from device

@@ -44,6 +44,7 @@ __device__ __forceinline__ int find_seq_sel(const LayerArgs& a, int b) {
 // Zero the selection control words and histograms (ckv_select on caller
 // scores; ckv_compress_layer clears them in the row-statistics kernel).
 __global__ __launch_bounds__(kThreads) void clear_kernel(const LayerArgs a) {
+  args_ready(args_touch<sizeof(LayerArgs)>());
   const int s = blockIdx.x / a.n_sg, g = blockIdx.x - s * a.n_sg;
   const SeqArgs& sq = a.seq[s];
   for (int i = threadIdx.x; i < kCtlWords; i += kThreads) sq.ctl[g * kCtlWords + i] = 0u;
@@ -53,6 +54,7 @@ __global__ __launch_bounds__(kThreads) void clear_kernel(const LayerArgs a) {
 
 // First-level histogram of caller-supplied scores, one range per workgroup.
 __global__ __launch_bounds__(kThreads) void hist_kernel(const LayerArgs a) {
+  args_ready(args_touch<sizeof(LayerArgs)>());
   __shared__ uint32_t hist_lds[kHistBins];
   const int b = blockIdx.x;
   const int s = find_seq_sel(a, b);
@@ -252,6 +254,7 @@ __device__ __forceinline__ void filter_body(const LayerArgs& a, int b) {
 }
 
 __global__ __launch_bounds__(kThreads) void filter_kernel(const LayerArgs a) {
+  args_ready(args_touch<sizeof(LayerArgs)>());
   filter_body(a, blockIdx.x);
 }
 
@@ -269,6 +272,7 @@ __device__ __forceinline__ void resolve_body(const LayerArgs& a, int b) {
 }
 
 __global__ __launch_bounds__(kThreads) void resolve_kernel(const LayerArgs a) {
+  args_ready(args_touch<sizeof(LayerArgs)>());
   resolve_body(a, blockIdx.x);
 }
 
@@ -391,6 +395,7 @@ __device__ __forceinline__ void compact_body(const LayerArgs& a, int b) {
 }
 
 __global__ __launch_bounds__(kThreads) void compact_kernel(const LayerArgs a) {
+  args_ready(args_touch<sizeof(LayerArgs)>());
   compact_body(a, blockIdx.x);
 }
 
@@ -417,6 +422,7 @@ __device__ __forceinline__ void gather_body(const LayerArgs& a, int b, int32_t* 
 
 // Standalone retain/evict (ckv_gather).
 __global__ __launch_bounds__(kThreads) void gather_kernel(const LayerArgs a) {
+  args_ready(args_touch<sizeof(LayerArgs)>());
   __shared__ int32_t tok_l[kGatherRows];
   gather_body(a, blockIdx.x, tok_l);
 }
