@@ -692,9 +692,6 @@ int ckv_allocate_budgets(const double* err_norm, int32_t n_layers, int64_t total
 // ---- compression-error profile ---------------------------------------------
 namespace {
 
-constexpr int kDecodeTargetWgs = 512;  // decode workgroups over all KV heads
-constexpr int kDecodeSlotsPerChunk = 4;
-
 int check_attn(const ckv_attn_desc* d, int32_t T) {
   if (!d || d->num_q_heads < 1 || d->num_kv_heads < 1 || d->num_q_heads % d->num_kv_heads)
     return CKV_ERR_INVALID_ARG;
@@ -727,22 +724,40 @@ int check_q(const ckv_attn_desc* d, const void* q, int64_t st, int64_t sh, int32
   return CKV_OK;
 }
 
-// Tokens per decode workgroup for one launch over caches of sum_n tokens in
-// all: about kDecodeTargetWgs workgroups over every KV head and prompt, each
-// at least one 32-token block, the same length for every prompt.
-int64_t decode_chunk_len(const ckv_attn_desc* d, int64_t sum_n) {
-  const int64_t c = ceil_div(sum_n * d->num_kv_heads, kDecodeTargetWgs);
-  return c <= 32 ? 32 : ceil_div(c, 32) * 32;
+// Query rows of one KV head.
+int32_t decode_rows(const ckv_attn_desc* d, int32_t T) {
+  return d->num_q_heads / d->num_kv_heads * T;
 }
 
-// Partial rows per slot: a group's T * (H / n_kv) query rows, whole 32-row blocks.
-int32_t decode_rows(const ckv_attn_desc* d, int32_t T) {
-  return (int32_t)(ceil_div((int64_t)(d->num_q_heads / d->num_kv_heads) * T, 32) * 32);
+// Tokens per decode workgroup for one launch over cnt caches of n[i] tokens, the
+// same for every prompt: a multiple of one 32-key tile, at least a tile per
+// wave, and long enough that the launch is one round of workgroups, two on
+// each CU (one where the kernel's registers or LDS admit only one). A few
+// workgroups more would run after the others: 516 of them took 122 us on
+// four caches of 196608 tokens in all, where 512 are resident at once.
+int64_t decode_chunk_len(const ckv_attn_desc* d, int32_t max_T, int32_t cnt, const int64_t* n) {
+  const bool one_per_cu = decode_rows(d, max_T) <= 64 &&
+                          (d->dtype == CKV_F32 || decode_rows(d, max_T) > 32);
+  const int64_t target = one_per_cu ? ckv::kCUs : 2 * ckv::kCUs;
+  int64_t sum_n = 0, max_n = 0;
+  for (int32_t i = 0; i < cnt; ++i) {
+    sum_n += n[i];
+    max_n = n[i] > max_n ? n[i] : max_n;
+  }
+  int64_t c = ceil_div(ceil_div(sum_n * d->num_kv_heads, target), 32) * 32;
+  if (c < 128) c = 128;
+  while (c < max_n) {
+    int64_t wgs = 0;
+    for (int32_t i = 0; i < cnt; ++i) wgs += ceil_div(n[i], c) * d->num_kv_heads;
+    if (wgs <= target) break;
+    c += ceil_div(c, 32 * 32) * 32;  // about 1/32 more
+  }
+  return c;
 }
 
 size_t decode_part_bytes(const ckv_attn_desc* d, int32_t T, int64_t n, int64_t chunk) {
-  return align_up((size_t)d->num_kv_heads * ceil_div(n, chunk) * kDecodeSlotsPerChunk *
-                  decode_rows(d, T) * (d->head_dim + 2) * sizeof(float));
+  return align_up((size_t)d->num_kv_heads * ceil_div(n, chunk) * decode_rows(d, T) *
+                  (d->head_dim + 2) * sizeof(float));
 }
 
 void decode_batch_init(const ckv_attn_desc* d, ckv::DecodeBatch& b) {
@@ -756,9 +771,10 @@ void decode_batch_init(const ckv_attn_desc* d, ckv::DecodeBatch& b) {
   b.mrg_off[0] = 0;
 }
 
-// Appends one prompt (its partials at part, chunk tokens per workgroup).
+// Appends one prompt (its partials at part, chunk tokens per workgroup). direct:
+// the launch's kernel can write out the result of a prompt of one chunk.
 void decode_batch_add(const ckv_attn_desc* d, const void* q, int64_t st, int64_t sh, int32_t T,
-                      const ckv_kv_cache* c, float* out, float* part, int64_t chunk,
+                      const ckv_kv_cache* c, float* out, float* part, int64_t chunk, bool direct,
                       ckv::DecodeBatch& b) {
   ckv::DecodeArgs& a = b.s[b.n];
   a.q = q;
@@ -772,14 +788,11 @@ void decode_batch_add(const ckv_attn_desc* d, const void* q, int64_t st, int64_t
   a.out = out;
   a.part = part;
   a.T = T;
-  a.prow = decode_rows(d, T);
   a.chunk = (int32_t)chunk;
   a.n_chunks = (int32_t)ceil_div(c->n, chunk);
-  a.n_slots = a.n_chunks * kDecodeSlotsPerChunk;
-  a.pad_ = 0;
-  const int64_t merge_elems = (int64_t)d->num_q_heads * T * d->head_dim;
+  a.direct = a.n_chunks == 1 && direct;
   b.blk_off[b.n + 1] = b.blk_off[b.n] + d->num_kv_heads * a.n_chunks;
-  b.mrg_off[b.n + 1] = b.mrg_off[b.n] + (int32_t)ceil_div(merge_elems, ckv::kDecodeThreads);
+  b.mrg_off[b.n + 1] = b.mrg_off[b.n] + (a.direct ? 0 : d->num_q_heads * T);
   ++b.n;
 }
 
@@ -809,18 +822,34 @@ int check_decode_seq(const ckv_attn_desc* d, const ckv_decode_seq* s) {
 int32_t decode_run(int32_t i0, int32_t num_seqs) {
   return num_seqs - i0 < ckv::kMaxDecodeSeqs ? num_seqs - i0 : ckv::kMaxDecodeSeqs;
 }
+int32_t decode_run_T(const ckv_decode_seq* seqs, int32_t i0, int32_t cnt) {
+  int32_t T = 0;
+  for (int32_t i = i0; i < i0 + cnt; ++i) T = seqs[i].T > T ? seqs[i].T : T;
+  return T;
+}
 int64_t decode_run_chunk(const ckv_attn_desc* d, const ckv_decode_seq* seqs, int32_t i0,
                          int32_t cnt) {
-  int64_t sum_n = 0;
-  for (int32_t i = i0; i < i0 + cnt; ++i) sum_n += seqs[i].cache.n;
-  return decode_chunk_len(d, sum_n);
+  int64_t n[ckv::kMaxDecodeSeqs];
+  for (int32_t i = 0; i < cnt; ++i) n[i] = seqs[i0 + i].cache.n;
+  return decode_chunk_len(d, decode_run_T(seqs, i0, cnt), cnt, n);
 }
+// Chunk length of a launch over one cache, or over a full and a compact one.
+int64_t decode_chunk_one(const ckv_attn_desc* d, int32_t T, int64_t n) {
+  return decode_chunk_len(d, T, 1, &n);
+}
+int64_t decode_chunk_two(const ckv_attn_desc* d, int32_t T, int64_t n0, int64_t n1) {
+  const int64_t n[2] = {n0, n1};
+  return decode_chunk_len(d, T, 2, n);
+}
+// Whether a launch whose largest prompt has T query tokens runs the kernel that
+// can write a one-chunk prompt's result.
+bool decode_direct(const ckv_attn_desc* d, int32_t T) { return decode_rows(d, T) <= 64; }
 
 }  // namespace
 
 size_t ckv_decode_workspace_bytes(const ckv_attn_desc* desc, int32_t T, int64_t n) {
   if (check_attn(desc, T) != CKV_OK || n < 1 || n >= ((int64_t)1 << 31)) return 0;
-  return decode_part_bytes(desc, T, n, decode_chunk_len(desc, n));
+  return decode_part_bytes(desc, T, n, decode_chunk_one(desc, T, n));
 }
 
 int ckv_decode_attention(const ckv_attn_desc* desc, const void* q, int64_t q_stride_t,
@@ -837,7 +866,7 @@ int ckv_decode_attention(const ckv_attn_desc* desc, const void* q, int64_t q_str
   ckv::DecodeBatch b;
   decode_batch_init(desc, b);
   decode_batch_add(desc, q, q_stride_t, q_stride_h, T, cache, out, static_cast<float*>(workspace),
-                   decode_chunk_len(desc, cache->n), b);
+                   decode_chunk_one(desc, T, cache->n), decode_direct(desc, T), b);
   const hipError_t e = ckv::launch_decode(desc->dtype, b, (hipStream_t)stream);
   return e == hipSuccess ? CKV_OK : hip_fail(e);
 }
@@ -874,10 +903,11 @@ int ckv_decode_attention_batch(const ckv_attn_desc* desc, const ckv_decode_seq* 
     const int64_t chunk = decode_run_chunk(desc, seqs, i0, cnt);
     ckv::DecodeBatch b;
     decode_batch_init(desc, b);
+    const bool direct = decode_direct(desc, decode_run_T(seqs, i0, cnt));
     for (int32_t i = i0; i < i0 + cnt; ++i) {
       const ckv_decode_seq& s = seqs[i];
       decode_batch_add(desc, s.q, s.q_stride_t, s.q_stride_h, s.T, &s.cache, s.out,
-                       reinterpret_cast<float*>(part), chunk, b);
+                       reinterpret_cast<float*>(part), chunk, direct, b);
       part += decode_part_bytes(desc, s.T, s.cache.n, chunk);
     }
     const hipError_t err = ckv::launch_decode(desc->dtype, b, (hipStream_t)stream);
@@ -892,7 +922,7 @@ size_t ckv_layer_error_workspace_bytes(const ckv_attn_desc* desc, int32_t T, int
       n_full >= ((int64_t)1 << 31) || n_comp >= ((int64_t)1 << 31))
     return 0;
   const size_t outs = align_up((size_t)T * desc->num_q_heads * desc->head_dim * sizeof(float));
-  const int64_t chunk = decode_chunk_len(desc, n_full + n_comp);
+  const int64_t chunk = decode_chunk_two(desc, T, n_full, n_comp);
   const size_t parts = decode_part_bytes(desc, T, n_full, chunk) + decode_part_bytes(desc, T, n_comp, chunk);
   const size_t proj = align_up((size_t)(ceil_div(D, 32) + 1) * 2 * T * sizeof(float));
   const int64_t K = (int64_t)desc->num_q_heads * desc->head_dim;
@@ -926,7 +956,7 @@ int ckv_layer_error(const ckv_attn_desc* desc, const void* q, int64_t q_stride_t
   float* a_comp = reinterpret_cast<float*>(ws + outs);
   char* part = ws + 2 * outs;
   // both decodes in one batch: the full cache and the compressed one
-  const int64_t chunk = decode_chunk_len(desc, full->n + comp->n);
+  const int64_t chunk = decode_chunk_two(desc, T, full->n, comp->n);
   const size_t pa = decode_part_bytes(desc, T, full->n, chunk);
   const size_t pb = decode_part_bytes(desc, T, comp->n, chunk);
   float* proj = reinterpret_cast<float*>(part + pa + pb);
@@ -936,9 +966,9 @@ int ckv_layer_error(const ckv_attn_desc* desc, const void* q, int64_t q_stride_t
   ckv::DecodeBatch db;
   decode_batch_init(desc, db);
   decode_batch_add(desc, q, q_stride_t, q_stride_h, T, full, a_full, reinterpret_cast<float*>(part),
-                   chunk, db);
+                   chunk, decode_direct(desc, T), db);
   decode_batch_add(desc, q, q_stride_t, q_stride_h, T, comp, a_comp,
-                   reinterpret_cast<float*>(part + pa), chunk, db);
+                   reinterpret_cast<float*>(part + pa), chunk, decode_direct(desc, T), db);
   hipError_t err;
   if ((err = ckv::launch_decode(desc->dtype, db, st)) != hipSuccess) return hip_fail(err);
   ckv::ErrorArgs ea;

@@ -3,15 +3,16 @@
 // full or a compressed KV cache, and the W_O-projected error ratio of every
 // decoding step.
 //
-// decode_kernel: one workgroup per (KV head g, chunk of the cache). The
-//   query rows of the group (its G heads x T tokens, head-major) are split
-//   into 32-row blocks; each wave keeps one block in registers and walks the
-//   chunk's 32-key blocks (waves sharing a query block take alternate key
-//   blocks). Per key block: S^T = K Q^T (keys x rows) with fp32 MFMA, an
-//   online max and sum per row, P = exp2(S - m), O += P V with fp32 MFMA.
-//   Every wave writes its rows' (max, sum, O) as one partial.
-// decode_merge_kernel: per (KV head, row): the partials rescaled to the
-//   common max and summed, divided by the sum: out[t][h][:].
+// decode_kernel: one workgroup per (KV head g, chunk of the cache), for up to
+//   64 query rows (a group's G heads x T tokens, head-major) in 32-row blocks.
+//   Each wave walks 32-key tiles of its own, staged in LDS that no other wave
+//   touches, so the loop has no barrier. Per tile: S^T = K Q^T (keys x rows)
+//   with MFMA, an online max and sum per row, P = exp2(S - m), O += P V with
+//   MFMA. The waves' (max, sum, O) meet in LDS and leave as one partial.
+// decode_rows_kernel_16 / _f32: the same for 65 to 128 query rows, a 32-row
+//   block per wave and the key tiles shared by the workgroup.
+// decode_merge_kernel: per (KV head, row): the chunks' partials rescaled to
+//   the common max and summed, divided by the sum: out[t][h][:].
 // project_kernel: Y = W_O X for the 2T columns X = [A_full | A_comp - A_full]
 //   with fp32 MFMA, one workgroup per 32 rows of W_O and 32 columns, then the
 //   column sums of Y^2 over its rows as one partial.
@@ -20,7 +21,7 @@
 // Everything accumulates in fp32: the ratios compare two attention outputs
 // that may differ in their third digit, which plain bf16 products would
 // blur. fp32 inputs use fp32 MFMA (32x32x2); 16-bit inputs use 16-bit MFMA
-// with the queries and probabilities split into high and low parts.
+// with the probabilities split into high and low parts.
 #include <math.h>
 
 #include "ckv_device.h"
@@ -81,10 +82,17 @@ __device__ __forceinline__ void load_row16(const void* base, int64_t off, float*
 }
 
 // ---------------------------------------------------------------------------
-// Decode attention, partials per (KV head, chunk, wave).
+// Decode attention, one partial per (KV head, chunk).
 // ---------------------------------------------------------------------------
+// The (max in exp2 units, sum) pairs [n_kv][n_chunks][R] that follow a
+// prompt's O partials [n_kv][n_chunks][R][d].
+__device__ __forceinline__ float2* partial_ml(const DecodeArgs& a, int n_kv, int R, int D) {
+  return reinterpret_cast<float2*>(a.part + (int64_t)n_kv * a.n_chunks * R * D);
+}
+
 template <int DT, int D>
-__global__ __launch_bounds__(kDecThreads) void decode_kernel_f32(const DecodeBatch B) {
+__global__ __launch_bounds__(kDecThreads) void decode_rows_kernel_f32(const DecodeBatch B) {
+  args_ready(args_touch<sizeof(DecodeBatch)>());
   constexpr int KB = 32;      // keys per block
   constexpr int KS = D + 1;   // LDS row stride: lanes reading one column of 32 rows hit 32 banks
   __shared__ float kl[KB * KS];  // K block [key][d], fp32
@@ -99,10 +107,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel_f32(const DecodeBat
   const int g = lb / a.n_chunks, chunk = lb - g * a.n_chunks;
   const int G = B.H / B.n_kv;
   const int R = G * a.T;                    // query rows of the group
-  const int nqb = (R + 31) >> 5;            // their 32-row blocks (<= kDecWaves)
-  const int wpq = kDecWaves / (nqb == 3 ? 4 : nqb);  // waves per query block
-  const int qb = wave / wpq, sub = wave - qb * wpq;
-  const bool active = qb < nqb;
+  const int qb = wave;                      // this wave's 32-row block of them
+  const bool active = qb * 32 < R;
   const int64_t j0 = (int64_t)chunk * a.chunk;
   const int64_t j1 = j0 + a.chunk < a.n ? j0 + a.chunk : a.n;
   const int nkb = (int)((j1 - j0 + KB - 1) / KB);
@@ -163,7 +169,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel_f32(const DecodeBat
     }
     __syncthreads();
     if (kb + 1 < nkb) issue(kb + 1);
-    if (active && (kb % wpq) == sub) {
+    if (active) {
       // S^T[key][row]: lane (row l32, half h) receives keys acc_row(v, h)
       f32x16 s = f32x16{};
 #pragma unroll
@@ -203,58 +209,58 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel_f32(const DecodeBat
   if (!active) return;
   // the partial of this wave: (max, sum) per row, and O rows
   l_run += __shfl_xor(l_run, 32);
-  const int slot = chunk * wpq + sub;
-  float* part = a.part + (((int64_t)g * a.n_slots + slot) * a.prow + qb * 32) * (D + 2);
-  if (h == 0) {
-    part[l32 * (D + 2) + D] = m_run;
-    part[l32 * (D + 2) + D + 1] = l_run;
-  }
+  if (!row_ok) return;
+  const int64_t slot = (int64_t)g * a.n_chunks + chunk;
+  if (h == 0) partial_ml(a, B.n_kv, R, D)[slot * R + r] = make_float2(m_run, l_run);
+  float* part = a.part + (slot * R + r) * D;
   // o[nb][v]: O^T[nb*32 + acc_row(v, h)][row l32]
 #pragma unroll
   for (int nb = 0; nb < D / 32; ++nb)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) part[l32 * (D + 2) + nb * 32 + acc_row(v, h)] = o[nb][v];
+    for (int v = 0; v < 16; ++v) part[nb * 32 + acc_row(v, h)] = o[nb][v];
+}
+
+// 8 (16-bit) or 4 (fp32) fp32 values -> one operand chunk, and for 16-bit types
+// the chunk of the rounded remainders.
+template <int DT>
+__device__ __forceinline__ void split_chunk(const float* x, uint4& hi, uint4& lo) {
+  if constexpr (DT == 2) {
+    hi = make_uint4(__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]),
+                    __float_as_uint(x[3]));
+  } else if constexpr (DT == 0) {
+    bf16x8 h, l;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      h[i] = (__bf16)x[i];
+      l[i] = (__bf16)(x[i] - (float)h[i]);
+    }
+    hi = __builtin_bit_cast(uint4, h);
+    lo = __builtin_bit_cast(uint4, l);
+  } else {
+    f16x8 h, l;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      h[i] = (_Float16)x[i];
+      l[i] = (_Float16)(x[i] - (float)h[i]);
+    }
+    hi = __builtin_bit_cast(uint4, h);
+    lo = __builtin_bit_cast(uint4, l);
+  }
 }
 
 // 16-bit inputs (bf16, f16): the same decode with 16-bit MFMA (32x32x16) at
-// fp32-level accuracy. K and V are exact in the MFMA type; the queries and
-// the probabilities are split into a high part (rounded to the type) and a
-// low part (the rounded remainder), and each product is the sum of two MFMAs,
-// which leaves a relative error near 2^-16 (bf16) or 2^-22 (f16) instead of
+// fp32-level accuracy. Q, K and V are exact in the MFMA type; the
+// probabilities are split into a high part (rounded to the type) and a low
+// part (the rounded remainder), and O += P V is the sum of two MFMAs, which
+// leaves a relative error near 2^-16 (bf16) or 2^-22 (f16) instead of
 // 2^-8 or 2^-11.
-template <int DT>
-__device__ __forceinline__ uint32_t to16(float x) {
-  if constexpr (DT == 0) {  // round to nearest even
-    const uint32_t u = __float_as_uint(x);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-  } else {
-    return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)x);
-  }
-}
-template <int DT>
-__device__ __forceinline__ float from16(uint32_t b) {
-  if constexpr (DT == 0) return __uint_as_float(b << 16);
-  else return (float)__builtin_bit_cast(_Float16, (uint16_t)b);
-}
-// 8 values -> the high and low 16-bit parts, packed two per word.
-template <int DT>
-__device__ __forceinline__ void split8(const float* x, uint4& hi, uint4& lo) {
-  uint32_t hb[8], lb[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    hb[i] = to16<DT>(x[i]);
-    lb[i] = to16<DT>(x[i] - from16<DT>(hb[i]));
-  }
-  hi = make_uint4(hb[0] | hb[1] << 16, hb[2] | hb[3] << 16, hb[4] | hb[5] << 16, hb[6] | hb[7] << 16);
-  lo = make_uint4(lb[0] | lb[1] << 16, lb[2] | lb[3] << 16, lb[4] | lb[5] << 16, lb[6] | lb[7] << 16);
-}
-
 // Blocks of 64 keys keep the staging registers small enough for two
 // workgroups per CU (two waves per SIMD): one workgroup reduces a block while
 // the other's loads are in flight.
 template <int DT, int D>
 __global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(2)))
-void decode_kernel_16(const DecodeBatch B) {
+void decode_rows_kernel_16(const DecodeBatch B) {
+  args_ready(args_touch<sizeof(DecodeBatch)>());
   constexpr int SB = 32;              // keys per MFMA tile (a sub-block)
   constexpr int NSB = 2;              // sub-blocks staged per block
   constexpr int KB = SB * NSB;        // keys per block
@@ -272,30 +278,25 @@ void decode_kernel_16(const DecodeBatch B) {
   const int g = lb / a.n_chunks, chunk = lb - g * a.n_chunks;
   const int G = B.H / B.n_kv;
   const int R = G * a.T;
-  const int nqb = (R + 31) >> 5;
-  const int wpq = kDecWaves / (nqb == 3 ? 4 : nqb);
-  const int qb = wave / wpq, sub = wave - qb * wpq;
-  const bool active = qb < nqb;
+  const int qb = wave;  // this wave's 32-row block of the query rows
+  const bool active = qb * 32 < R;
   const int64_t j0 = (int64_t)chunk * a.chunk;
   const int64_t j1 = j0 + a.chunk < a.n ? j0 + a.chunk : a.n;
   const int nkb = (int)((j1 - j0 + KB - 1) / KB);
 
   // query row r = head-in-group * T + t; lane half h holds elements
-  // 16c + 8h .. 16c + 8h + 7 of it, split into high and low parts
+  // 16c + 8h .. 16c + 8h + 7 of it (exact: queries have the MFMA's type)
   const int r = qb * 32 + l32;
   const bool row_ok = active && r < R;
-  uint4 qh[NC], ql[NC];
+  uint4 qh[NC];
   {
     const int hl = row_ok ? r / a.T : 0, t = row_ok ? r - (r / a.T) * a.T : 0;
     const int64_t qoff = (int64_t)t * a.q_st + (int64_t)(g * G + hl) * a.q_sh;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      float x[8];
-      if (row_ok) load_row16<DT>(a.q, qoff + 16 * c + 8 * h, x);
-      else
-#pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = 0.f;
-      split8<DT>(x, qh[c], ql[c]);
+      const u32x4 x = *reinterpret_cast<const CKV_GLOBAL u32x4*>(
+          to_global(static_cast<const char*>(a.q)) + (qoff + 16 * c + 8 * h) * 2);
+      qh[c] = row_ok ? make_uint4(x.x, x.y, x.z, x.w) : make_uint4(0u, 0u, 0u, 0u);
     }
   }
   f32x16 o[D / 32];
@@ -306,8 +307,7 @@ void decode_kernel_16(const DecodeBatch B) {
   const int64_t kv_base = (int64_t)g * a.kv_sh;
 
   // every block of KB keys is staged by all threads (16-byte loads, the next
-  // block's issued before the current one is reduced); the waves of a query
-  // block split its sub-blocks, so every wave works on every block
+  // block's issued before the current one is reduced)
   constexpr int NLD = KB * D / 8 / kDecThreads;  // 16-byte loads per thread per block
   static_assert(NLD >= 1 && KB * D / 8 % kDecThreads == 0, "block loads");
   u32x4 kr[NLD], vr[NLD];
@@ -339,18 +339,17 @@ void decode_kernel_16(const DecodeBatch B) {
     }
     __syncthreads();
     if (kb + 1 < nkb) issue(kb + 1);
-    for (int sb = sub; active && sb < NSB; sb += wpq) {
+    for (int sb = 0; active && sb < NSB; ++sb) {
       const int64_t ts = t0 + sb * SB;  // first key of the sub-block
       if (ts >= j1) break;
-      // S^T[key][row] = K Q^T with Q = high + low parts; lane (row l32, half
-      // h) receives keys acc_row(v, h) of the sub-block
+      // S^T[key][row] = K Q^T; lane (row l32, half h) receives keys
+      // acc_row(v, h) of the sub-block
       f32x16 s = f32x16{};
       const unsigned char* krow = kl + (sb * SB + l32) * KROW;
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
         const uint4 kc = *reinterpret_cast<const uint4*>(krow + (16 * c + 8 * h) * 2);
         s = mfma_chunk<DT>(kc, qh[c], s);
-        s = mfma_chunk<DT>(kc, ql[c], s);
       }
       float mx = -INFINITY;
 #pragma unroll
@@ -379,8 +378,8 @@ void decode_kernel_16(const DecodeBatch B) {
           p0[i] = s[i];
           p1[i] = s[8 + i];
         }
-        split8<DT>(p0, ph[0], pl[0]);
-        split8<DT>(p1, ph[1], pl[1]);
+        split_chunk<DT>(p0, ph[0], pl[0]);
+        split_chunk<DT>(p1, ph[1], pl[1]);
       }
 #pragma unroll
       for (int nb = 0; nb < D / 32; ++nb) {
@@ -409,67 +408,397 @@ void decode_kernel_16(const DecodeBatch B) {
   }
   if (!active) return;
   l_run += __shfl_xor(l_run, 32);
-  const int slot = chunk * wpq + sub;
-  float* part = a.part + (((int64_t)g * a.n_slots + slot) * a.prow + qb * 32) * (D + 2);
-  if (h == 0) {
-    part[l32 * (D + 2) + D] = m_run;
-    part[l32 * (D + 2) + D + 1] = l_run;
-  }
+  if (!row_ok) return;
+  const int64_t slot = (int64_t)g * a.n_chunks + chunk;
+  if (h == 0) partial_ml(a, B.n_kv, R, D)[slot * R + r] = make_float2(m_run, l_run);
+  float* part = a.part + (slot * R + r) * D;
 #pragma unroll
   for (int nb = 0; nb < D / 32; ++nb)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) part[l32 * (D + 2) + nb * 32 + acc_row(v, h)] = o[nb][v];
+    for (int v = 0; v < 16; ++v) part[nb * 32 + acc_row(v, h)] = o[nb][v];
 }
 
-// out[t][h][c] from the partials of every slot, one thread per (row, c).
+// Wait until at most n vector-memory operations of this wave are outstanding
+// and its LDS operations are done; nothing is moved across.
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x070 | (N & 15) | ((N >> 4) << 14));
+  asm volatile("" ::: "memory");
+}
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// Up to 32 * NQ query rows. A cache row is read once, so the bound is the
+// stream: what counts is how much of it is in flight and that no wave waits
+// for another. Every wave therefore owns its tiles: 32 keys of K and of V go
+// straight from memory into the wave's part of LDS, and the next tile's K is
+// requested as soon as this tile's K is in registers, before its contraction
+// (the same for V), so a CU has 64 to 128 KB requested nearly all the time. V
+// is transposed for the second contraction by ds_read_b64_tr_b16 (16 reads a
+// tile; gathering it with 2-byte reads took 64 and as many packs). The waves'
+// results are added in LDS, and only rows that exist are written out.
+// Shared 64-key blocks behind two barriers, with half the waves idle at up to
+// 32 rows and a 32-row partial per wave, took 122 us + 27 us for the merge on
+// four caches of 8192 to 98304 tokens (402 MB of K and V); this takes 61 + 5 us,
+// 6.5 TB/s.
+template <int DT, int D, int NQ>
+__global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(DT != 2 && NQ == 1 ? 2 : 1)))
+void decode_kernel(const DecodeBatch B) {
+  constexpr int EB = Elt<DT>::bytes;
+  constexpr int ROWB = D * EB;       // bytes per cache row
+  constexpr int NV = ROWB / 16;      // 16-byte chunks per row: 8, 16 or 32
+  constexpr int NC = NV / 2;         // operand chunks per lane
+  constexpr int KT = 32;             // keys per tile
+  constexpr int VEC = KT * NV;       // 16-byte chunks per tile
+  constexpr int PT = VEC / 64;       // load instructions per tile
+  constexpr int RPL = 64 / NV;       // tile rows per load instruction
+  constexpr int NB = D / 32;
+  __shared__ uint4 kl[kDecWaves][VEC];  // chunk c of row t at position c ^ swz(t)
+  __shared__ uint4 vl[kDecWaves][VEC];
+  __shared__ float2 ml[kDecWaves][32];
+  const uint32_t touched = args_touch<sizeof(DecodeBatch)>();
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int si = 0;
+  while (si + 1 < B.n && (int)blockIdx.x >= B.blk_off[si + 1]) ++si;
+  const DecodeArgs& a = B.s[si];
+  const int lb = (int)blockIdx.x - B.blk_off[si];
+  const int g = lb / a.n_chunks, chunk = lb - g * a.n_chunks;
+  const int G = B.H / B.n_kv;
+  const int R = G * a.T;
+  const int64_t j0 = (int64_t)chunk * a.chunk;
+  const int64_t j1 = j0 + a.chunk < a.n ? j0 + a.chunk : a.n;
+  const int nt = (int)((j1 - j0 + KT - 1) / KT);
+  const int64_t rs = a.kv_st * EB;
+  const char* kbase = static_cast<const char*>(a.k) + ((int64_t)g * a.kv_sh + j0 * a.kv_st) * EB;
+  const char* vbase = static_cast<const char*>(a.v) + ((int64_t)g * a.kv_sh + j0 * a.kv_st) * EB;
+  const int rows = (int)(j1 - j0);
+  const float alpha = B.alpha;
+  args_ready(touched);
+
+  auto swz = [](int t) { return ROWB >= 256 ? (t & 15) : ((t >> 1) & 7); };
+  // load i of a tile brings rows i * RPL .. + RPL - 1; this lane's chunk of row
+  // t goes to position lane % NV, so it is chunk (lane % NV) ^ swz(t)
+  const int lrow = lane / NV, lpos = lane % NV;
+  const int64_t lane_off = lrow * rs;
+  // tile tl of base: non-temporal, each cache row is read once. Rows past the
+  // chunk read its last row instead.
+  auto fetch = [&](const char* base, int tl, uint4* slot) {
+    const char* tb = base + (int64_t)tl * KT * rs;
+    if (tl * KT + KT <= rows) {
+#pragma unroll
+      for (int i = 0; i < PT; ++i)
+        __builtin_amdgcn_global_load_lds(
+            reinterpret_cast<const uint4*>(tb + (int64_t)i * RPL * rs + lane_off +
+                                           (lpos ^ swz(i * RPL + lrow)) * 16),
+            slot + i * 64, 16, 0, 2);
+    } else {
+#pragma unroll
+      for (int i = 0; i < PT; ++i) {
+        const int t = i * RPL + lrow;
+        const int tc = tl * KT + t < rows ? t : rows - 1 - tl * KT;
+        __builtin_amdgcn_global_load_lds(
+            reinterpret_cast<const uint4*>(tb + tc * rs + (lpos ^ swz(t)) * 16), slot + i * 64, 16,
+            0, 2);
+      }
+    }
+  };
+  int tile = wave;
+  if (tile < nt) {
+    fetch(kbase, tile, kl[wave]);
+    fetch(vbase, tile, vl[wave]);
+  }
+
+  // query row r = head-in-group * T + t; lane half h holds chunks 2c + h of it,
+  // 16-bit queries exactly (alpha is applied to the logits)
+  uint4 q[NQ][NC];
+#pragma unroll
+  for (int j = 0; j < NQ; ++j) {
+    const int r = j * 32 + l32;
+    const bool row_ok = r < R;
+    const int hl = row_ok ? r / a.T : 0, t = row_ok ? r - hl * a.T : 0;
+    const int64_t qoff = ((int64_t)t * a.q_st + (int64_t)(g * G + hl) * a.q_sh) * EB;
+    const CKV_GLOBAL u32x4* src =
+        (const CKV_GLOBAL u32x4*)(to_global(static_cast<const char*>(a.q)) + qoff) + h;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const u32x4 x = src[2 * c];
+      q[j][c] = row_ok ? make_uint4(x.x, x.y, x.z, x.w) : make_uint4(0u, 0u, 0u, 0u);
+    }
+  }
+  f32x16 o[NQ][NB];
+  float m_run[NQ], l_run[NQ];  // the maximum is of the unscaled logits
+#pragma unroll
+  for (int j = 0; j < NQ; ++j) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) o[j][nb] = f32x16{};
+    m_run[j] = -INFINITY;
+    l_run[j] = 0.f;
+  }
+  // byte offset of V chunk column group (nb, jj) in a 16-key half of the tile:
+  // lane i of a 16-lane group reads columns 4 * (i % 4) .. + 3 of key
+  // 8 * jj + 4 * h + i / 4, and receives column i of the 4 keys
+  const int i16 = lane & 15;
+  auto v_off = [&](int nb, int jj) {
+    const int key = 8 * jj + 4 * h + (i16 >> 2);
+    const int col = nb * 32 + (lane & 16) + 4 * (i16 & 3);
+    return key * ROWB + ((col >> 3) ^ swz(key)) * 16 + (col & 7) * 2;
+  };
+
+  for (; tile < nt; tile += kDecWaves) {
+    const bool more = tile + kDecWaves < nt;
+    wait_vm<PT>();  // this tile's K; its V may still be on the way
+    uint4 kr[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) kr[c] = kl[wave][l32 * NV + ((2 * c + h) ^ swz(l32))];
+    wait_vm<63>();  // K is in registers: its part of LDS is free
+    if (more) fetch(kbase, tile + kDecWaves, kl[wave]);
+    const int left = rows - tile * KT;  // keys of this tile that exist, if below KT
+    f32x16 s[NQ];
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) s[j] = f32x16{};
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int j = 0; j < NQ; ++j) s[j] = mfma_chunk<DT>(kr[c], q[j][c], s[j]);
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+      if (left < KT) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (acc_row(v, h) >= left) s[j][v] = -INFINITY;
+      }
+      float mx = s[j][0];
+#pragma unroll
+      for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[j][v]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      const float m_new = fmaxf(m_run[j], mx);
+      const float ms = m_new == -INFINITY ? 0.f : m_new * alpha;
+      if (__any(m_new > m_run[j])) {  // some row's maximum moved: rescale
+        const float resc = m_run[j] == -INFINITY ? 0.f : fast_exp2(m_run[j] * alpha - ms);
+        l_run[j] *= resc;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) o[j][nb] *= resc;
+        m_run[j] = m_new;
+      }
+      float psum = 0.f;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        s[j][v] = fast_exp2(fmaf(s[j][v], alpha, -ms));
+        psum += s[j][v];
+      }
+      l_run[j] += psum;
+    }
+    if (more) wait_vm<PT>();  // this tile's V; the next K may still be on the way
+    else wait_vm<0>();
+    if (left < KT) {  // rows past the chunk count as zeros
+#pragma unroll
+      for (int i = 0; i < PT; ++i)
+        if (i * RPL + lrow >= left) vl[wave][i * 64 + lane] = make_uint4(0u, 0u, 0u, 0u);
+      wait_vm<63>();
+    }
+    const char* vt = reinterpret_cast<const char*>(vl[wave]);
+    if constexpr (DT != 2) {
+      // P^T operands: MFMA step m takes this lane's keys acc_row(8m .. 8m+7, h)
+      // = 16m + 4h + (0..3) and 16m + 8 + 4h + (0..3), in that order
+      uint4 vr[2][NB];
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          typedef __attribute__((address_space(3))) s16x4* LdsPtr;
+          const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (LdsPtr)(vt + v_off(nb, 0) + m * 16 * ROWB));
+          const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (LdsPtr)(vt + v_off(nb, 1) + m * 16 * ROWB));
+          const uint2 a2 = __builtin_bit_cast(uint2, lo4), b2 = __builtin_bit_cast(uint2, hi4);
+          vr[m][nb] = make_uint4(a2.x, a2.y, b2.x, b2.y);
+        }
+      wait_vm<63>();  // V is in registers
+      if (more) fetch(vbase, tile + kDecWaves, vl[wave]);
+#pragma unroll
+      for (int j = 0; j < NQ; ++j)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          float p[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) p[i] = s[j][8 * m + i];
+          uint4 ph, pl;
+          split_chunk<DT>(p, ph, pl);
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) o[j][nb] = mfma_chunk<DT>(vr[m][nb], ph, o[j][nb]);
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) o[j][nb] = mfma_chunk<DT>(vr[m][nb], pl, o[j][nb]);
+        }
+    } else {
+      auto v_elem = [&](int v, int nb) {
+        const int key = acc_row(v, h), col = nb * 32 + l32;
+        return *reinterpret_cast<const float*>(vt + key * ROWB + ((col >> 2) ^ swz(key)) * 16 +
+                                               (col & 3) * 4);
+      };
+      if constexpr (NQ == 1) {
+        float vr[16][NB];
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) vr[v][nb] = v_elem(v, nb);
+        wait_vm<63>();
+        if (more) fetch(vbase, tile + kDecWaves, vl[wave]);
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) o[0][nb] = mfma_f32(vr[v][nb], s[0][v], o[0][nb]);
+      } else {
+        // the fp32 queries and outputs of two query blocks leave no registers
+        // for a whole tile of V: it is read along, and requested after
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) {
+            const float x = v_elem(v, nb);
+#pragma unroll
+            for (int j = 0; j < NQ; ++j) o[j][nb] = mfma_f32(x, s[j][v], o[j][nb]);
+          }
+        wait_vm<63>();
+        if (more) fetch(vbase, tile + kDecWaves, vl[wave]);
+      }
+    }
+  }
+
+  // the waves' results, rescaled to the common maximum and added in wave order,
+  // one query block at a time through the tiles' LDS. A wave's O^T (32 rows of
+  // D floats) fills its K and V parts when elements are 2 bytes (columns below
+  // and from D / 2), its K part when they are 4. 16-byte chunks of row r are
+  // XOR-ed with r % 8.
+  constexpr int OC = EB == 2 ? D / 8 : D / 4;  // 16-byte chunks of a row in one part
+  float2* pml = partial_ml(a, B.n_kv, R, D);
+  const int64_t slot = (int64_t)g * a.n_chunks + chunk;
+#pragma unroll
+  for (int j = 0; j < NQ; ++j) {
+    if (j * 32 >= R) break;
+    __syncthreads();
+    const float l = l_run[j] + __shfl_xor(l_run[j], 32);
+    if (h == 0)
+      ml[wave][l32] = make_float2(m_run[j] == -INFINITY ? -INFINITY : m_run[j] * alpha, l);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) {
+        const int c = nb * 8 + v4 * 2 + h;  // chunk of the row: columns 4c .. 4c + 3
+        float4* part = reinterpret_cast<float4*>(c < OC ? kl[wave] : vl[wave]);
+        part[l32 * OC + ((c % OC) ^ (l32 & 7))] =
+            make_float4(o[j][nb][4 * v4], o[j][nb][4 * v4 + 1], o[j][nb][4 * v4 + 2],
+                        o[j][nb][4 * v4 + 3]);
+      }
+    __syncthreads();
+    const int n_rows = R - j * 32 < 32 ? R - j * 32 : 32;
+    for (int e = tid; e < n_rows * (D / 4); e += kDecThreads) {
+      const int rr = e / (D / 4), c = e - rr * (D / 4), r = j * 32 + rr;
+      float m = ml[0][rr].x;
+#pragma unroll
+      for (int w = 1; w < kDecWaves; ++w) m = fmaxf(m, ml[w][rr].x);
+      float ls = 0.f;
+      float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int w = 0; w < kDecWaves; ++w) {
+        const float2 x = ml[w][rr];
+        if (x.x == -INFINITY) continue;  // a wave without keys
+        const float f = exp2f(x.x - m);
+        const float4* part = reinterpret_cast<const float4*>(c < OC ? kl[w] : vl[w]);
+        const float4 y = part[rr * OC + ((c % OC) ^ (rr & 7))];
+        ls += x.y * f;
+        acc.x += y.x * f;
+        acc.y += y.y * f;
+        acc.z += y.z * f;
+        acc.w += y.w * f;
+      }
+      if (a.direct) {  // the only chunk: the result itself (4-byte aligned)
+        const int hl = r / a.T, t = r - hl * a.T;
+        float* out = a.out + ((int64_t)t * B.H + g * G + hl) * D + 4 * c;
+        out[0] = acc.x / ls;
+        out[1] = acc.y / ls;
+        out[2] = acc.z / ls;
+        out[3] = acc.w / ls;
+      } else {
+        *reinterpret_cast<float4*>(a.part + (slot * R + r) * D + 4 * c) = acc;
+        if (c == 0) pml[slot * R + r] = make_float2(m, ls);
+      }
+    }
+  }
+}
+
+// out[t][h][:] from the chunks' partials, one workgroup per (prompt, query
+// row): D / 4 lanes take four columns each, and the 256 / (D / 4) thread groups
+// take every such chunk in turn with U of them in flight, then meet in LDS in a
+// fixed order. One thread per output walking all slots 16 at a time was a
+// chain of up to 16 trips to memory (27 us for four caches of 8192 to 98304
+// tokens, now 4.7 us).
 template <int D>
 __global__ __launch_bounds__(kDecThreads) void decode_merge_kernel(const DecodeBatch B) {
+  constexpr int C4 = D / 4, NG = kDecThreads / C4, U = 8;
+  __shared__ float4 acc_l[NG][C4];
+  __shared__ float2 ml_l[NG];
+  args_ready(args_touch<sizeof(DecodeBatch)>());
   int si = 0;
   while (si + 1 < B.n && (int)blockIdx.x >= B.mrg_off[si + 1]) ++si;
   const DecodeArgs& a = B.s[si];
   const int G = B.H / B.n_kv;
   const int R = G * a.T;
-  const int64_t e = (int64_t)((int)blockIdx.x - B.mrg_off[si]) * kDecThreads + threadIdx.x;
-  const int64_t per_g = (int64_t)R * D;
-  if (e >= per_g * B.n_kv) return;
-  const int g = (int)(e / per_g);
-  const int rc = (int)(e - (int64_t)g * per_g);
-  const int r = rc / D, c = rc - r * D;
-  const int nqb = (R + 31) >> 5;
-  const int wpq = kDecWaves / (nqb == 3 ? 4 : nqb);
-  const int n_used = a.n_chunks * wpq;
-  const CKV_GLOBAL float* base = to_global(a.part) + ((int64_t)g * a.n_slots * a.prow + r) * (D + 2);
-  const int64_t stride = (int64_t)a.prow * (D + 2);
-  // one pass over the slots, U at a time, with the running maximum: the sums
-  // are rescaled whenever a slot's maximum exceeds it
-  constexpr int U = 16;  // slots loaded at once
-  float m = -INFINITY, l = 0.f, acc = 0.f;
-  for (int s0 = 0; s0 < n_used; s0 += U) {
-    float ms[U], ls[U], os[U];
+  const int lr = (int)blockIdx.x - B.mrg_off[si];
+  const int g = lr / R, r = lr - g * R;
+  const int c = threadIdx.x % C4, ng = threadIdx.x / C4;
+  const int n = a.n_chunks;
+  const CKV_GLOBAL f32x4* po =
+      (const CKV_GLOBAL f32x4*)to_global(a.part) + ((int64_t)g * n * R + r) * C4 + c;
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  const CKV_GLOBAL f32x2* pm =
+      (const CKV_GLOBAL f32x2*)to_global(partial_ml(a, B.n_kv, R, D)) + (int64_t)g * n * R + r;
+  // running maximum: the sums are rescaled whenever a chunk's exceeds it
+  float m = -INFINITY, l = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int s0 = ng; s0 < n; s0 += NG * U) {
+    f32x2 x[U];
+    f32x4 y[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const bool in = s0 + u < n_used;
-      const CKV_GLOBAL float* p = base + (in ? s0 + u : 0) * stride;
-      ms[u] = in ? p[D] : -INFINITY;
-      ls[u] = p[D + 1];
-      os[u] = p[c];
+      const int s = s0 + u * NG < n ? s0 + u * NG : s0;
+      x[u] = pm[(int64_t)s * R];
+      y[u] = po[(int64_t)s * R * C4];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (ms[u] == -INFINITY) continue;  // a slot that saw no key, or past the last
-      if (ms[u] > m) {
-        const float f = exp2f(m - ms[u]);  // 0 while nothing has been added
+      if (s0 + u * NG >= n || x[u].x == -INFINITY) continue;
+      if (x[u].x > m) {
+        const float f = exp2f(m - x[u].x);  // 0 while nothing has been added
         l *= f;
         acc *= f;
-        m = ms[u];
+        m = x[u].x;
       }
-      const float f = exp2f(ms[u] - m);
-      l += ls[u] * f;
-      acc += os[u] * f;
+      const float f = exp2f(x[u].x - m);
+      l += x[u].y * f;
+      acc += y[u] * f;
     }
   }
+  acc_l[ng][c] = make_float4(acc.x, acc.y, acc.z, acc.w);
+  if (c == 0) ml_l[ng] = make_float2(m, l);
+  __syncthreads();
+  if (threadIdx.x >= D) return;
+  // thread d adds column d of every group
+  const int d = threadIdx.x;
+  float mm = ml_l[0].x;
+#pragma unroll
+  for (int i = 1; i < NG; ++i) mm = fmaxf(mm, ml_l[i].x);
+  float ls = 0.f, s = 0.f;
+#pragma unroll
+  for (int i = 0; i < NG; ++i) {
+    if (ml_l[i].x == -INFINITY) continue;
+    const float f = exp2f(ml_l[i].x - mm);
+    ls += ml_l[i].y * f;
+    s += reinterpret_cast<const float*>(&acc_l[i][d / 4])[d & 3] * f;
+  }
   const int hl = r / a.T, t = r - hl * a.T;
-  a.out[((int64_t)t * B.H + g * G + hl) * D + c] = acc / l;
+  a.out[((int64_t)t * B.H + g * G + hl) * D + d] = s / ls;
 }
 
 // ---------------------------------------------------------------------------
@@ -771,31 +1100,31 @@ __global__ __launch_bounds__(kDecThreads) void error_kernel(const ErrorArgs a) {
   }
 }
 
-template <template <int, int> class KernelOf>
-hipError_t launch_dec(int dtype, int d, const DecodeBatch& b, int grid, hipStream_t st) {
-  const Timing tm;
-  if (dtype == 0) return d == 64 ? launch(KernelOf<0, 64>::fn, grid, kDecThreads, st, tm, b)
-                                 : launch(KernelOf<0, 128>::fn, grid, kDecThreads, st, tm, b);
-  if (dtype == 1) return d == 64 ? launch(KernelOf<1, 64>::fn, grid, kDecThreads, st, tm, b)
-                                 : launch(KernelOf<1, 128>::fn, grid, kDecThreads, st, tm, b);
-  return d == 64 ? launch(KernelOf<2, 64>::fn, grid, kDecThreads, st, tm, b)
-                 : launch(KernelOf<2, 128>::fn, grid, kDecThreads, st, tm, b);
-}
-
+// The decode kernel of a batch whose largest prompt has `rows` query rows per
+// KV head.
 template <int DT, int D>
-struct DecodeOf {
-  static constexpr auto fn = decode_kernel_16<DT, D>;
-};
-template <int D>
-struct DecodeOf<2, D> {
-  static constexpr auto fn = decode_kernel_f32<2, D>;
-};
+hipError_t launch_dec(const DecodeBatch& b, int rows, hipStream_t st) {
+  const Timing tm;
+  const int grid = b.blk_off[b.n];
+  if (rows <= 32) return launch(decode_kernel<DT, D, 1>, grid, kDecThreads, st, tm, b);
+  if (rows <= 64) return launch(decode_kernel<DT, D, 2>, grid, kDecThreads, st, tm, b);
+  if constexpr (DT == 2) return launch(decode_rows_kernel_f32<2, D>, grid, kDecThreads, st, tm, b);
+  else return launch(decode_rows_kernel_16<DT, D>, grid, kDecThreads, st, tm, b);
+}
 
 }  // namespace
 
 hipError_t launch_decode(int dtype, const DecodeBatch& b, hipStream_t st) {
-  hipError_t e = launch_dec<DecodeOf>(dtype, b.d, b, b.blk_off[b.n], st);
-  if (e != hipSuccess) return e;
+  int rows = 0;
+  for (int i = 0; i < b.n; ++i) {
+    const int r = b.H / b.n_kv * b.s[i].T;
+    rows = r > rows ? r : rows;
+  }
+  hipError_t e;
+  if (dtype == 0) e = b.d == 64 ? launch_dec<0, 64>(b, rows, st) : launch_dec<0, 128>(b, rows, st);
+  else if (dtype == 1) e = b.d == 64 ? launch_dec<1, 64>(b, rows, st) : launch_dec<1, 128>(b, rows, st);
+  else e = b.d == 64 ? launch_dec<2, 64>(b, rows, st) : launch_dec<2, 128>(b, rows, st);
+  if (e != hipSuccess || b.mrg_off[b.n] == 0) return e;
   const Timing tm;
   return b.d == 64 ? launch(decode_merge_kernel<64>, b.mrg_off[b.n], kDecThreads, st, tm, b)
                    : launch(decode_merge_kernel<128>, b.mrg_off[b.n], kDecThreads, st, tm, b);

@@ -187,18 +187,17 @@ struct DecodeArgs {
   int64_t kv_sh, kv_st;
   int64_t n;               // cached tokens
   float* out;              // [T][H][d] fp32
-  float* part;             // [n_kv][n_slots][prow][d + 2]: O rows, then (max, sum)
+  float* part;             // [n_kv][n_chunks][R][d] O rows of the R query rows per KV head,
+                           // then [n_kv][n_chunks][R] (max, sum)
   int32_t T;
-  int32_t prow;            // partial rows per slot: the group's query rows rounded up to 32
   int32_t chunk;           // cached tokens per workgroup
   int32_t n_chunks;
-  int32_t n_slots;         // partial slots per KV head: n_chunks * 4
-  int32_t pad_;
+  int32_t direct;          // one chunk: its workgroups write out themselves, nothing to merge
 };
 
 // Up to kMaxDecodeSeqs prompts (ragged caches) in one pair of launches: the
 // decode workgroups of prompt i are [blk_off[i], blk_off[i+1]), its merge
-// workgroups [mrg_off[i], mrg_off[i+1]).
+// workgroups (one per query row, none when direct) [mrg_off[i], mrg_off[i+1]).
 constexpr int kProjSplit = 16;     // fewest K ranges of the W_O projection (partial tiles added in order)
 constexpr int kProjRangeK = 256;   // most k per K range of the 16-bit projection
 // K ranges of the W_O projection for K = H * d columns of W_O.
