@@ -332,9 +332,28 @@ int run_score(const ckv_layer_desc* d, const ckv::LayerArgs& a, hipStream_t st) 
   return rc != CKV_OK ? rc : run_pool(a, st);
 }
 
+// Parts per selection unit of one layer, or 0 when a prompt is too long for
+// every part to read its scores (kPartTokens). The parts of all units together are one round
+// of workgroups (the unit kernel's LDS admits one per CU), each with at least
+// kPartRows rows to copy; without copies there is nothing to share out.
+int32_t unit_parts(const ckv::LayerArgs& a) {
+  int64_t rows = 1;
+  for (int32_t i = 0; i < a.num_seqs; ++i) {
+    const ckv::SeqArgs& q = a.seq[i];
+    if (q.L - a.tail > (a.do_gather ? ckv::kPartTokens : ckv::kPartTokensNoCopy)) return 0;
+    const int64_t r = (int64_t)q.n_ret * (a.shared ? a.n_kv : 1);
+    rows = r > rows ? r : rows;
+  }
+  if (!a.do_gather) return 1;
+  const int64_t most = ckv::kCUs / (a.num_seqs * a.n_sg), useful = ceil_div(rows, ckv::kPartRows);
+  const int64_t n = most < useful ? most : useful;
+  return n < 1 ? 1 : (int32_t)n;
+}
+
 // Selection on scores already in place. With caller scores (ckv_select) the
 // control words and histograms are built here; in ckv_compress_layer the
-// scoring kernel built them.
+// scoring kernel built them. Prompts up to kPartTokens take one launch from the
+// threshold to the copied rows, longer ones the ranges of every unit in three.
 int run_select(const ckv::LayerArgs& a, bool caller_scores, hipStream_t st) {
   hipError_t e;
   const int gs = grid_sel(a);
@@ -344,6 +363,13 @@ int run_select(const ckv::LayerArgs& a, bool caller_scores, hipStream_t st) {
         hipSuccess)
       return hip_fail(e);
     if ((e = ckv::launch_hist(a, gs, st, none)) != hipSuccess) return hip_fail(e);
+  }
+  const int32_t parts = unit_parts(a);
+  if (parts > 0) {
+    ckv::Timing tm = timing(ckv::kStageSelect, !caller_scores, false);
+    tm.stop = timing(ckv::kStageGather, false, true).stop;
+    e = ckv::launch_select_parts(a, parts, st, tm);
+    return e == hipSuccess ? CKV_OK : hip_fail(e);
   }
   if ((e = ckv::launch_filter(a, gs, st, timing(ckv::kStageSelect, !caller_scores, false))) !=
       hipSuccess)

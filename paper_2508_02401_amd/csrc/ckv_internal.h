@@ -31,6 +31,17 @@ constexpr int kGatherRows = 64;    // retained rows per gather workgroup
 // A selection batch whose largest unit keeps more rows than this copies them
 // in a gather launch of its own: one workgroup per unit copies too slowly.
 constexpr int kUnitCopyRows = 512;
+// Scored tokens that a selection unit reads once (its LDS bitmaps), and the most
+// that one layer's units are split into parts for, with and without copies of
+// the kept rows: every part reads all of a unit's scores (1.6 us per 16384),
+// where the filter, resolve and compact launches share them out. With copies,
+// 8 KV heads: 32768 tokens, 2048 kept: 20 us against 32 us for the three
+// launches; 131072 tokens, 1024 kept: 28 against 26 us. Without copies: 65533
+// tokens, 2048 kept: 22 against 20 us.
+constexpr int64_t kUnitTokens = 131072;
+constexpr int64_t kPartTokens = 65536;
+constexpr int64_t kPartTokensNoCopy = 32768;
+constexpr int kPartRows = 16;      // kept rows per part of a split selection unit (at least)
 constexpr int kHistBits = 12;      // first-level histogram: key bits 30..19
 constexpr int kHistBins = 1 << kHistBits;
 constexpr int kHistShift = 31 - kHistBits;
@@ -270,6 +281,8 @@ hipError_t launch_decode(int dtype, const DecodeBatch& b, hipStream_t st);
 hipError_t launch_stream_gather(const LayerArgs& a, int32_t sinks, int grid, hipStream_t st);
 hipError_t launch_error(int w_dtype, const ErrorArgs& a, hipStream_t st);
 hipError_t launch_select_units(const MultiArgs& m, hipStream_t st, const Timing& tm);
+// The same for one layer, n_parts workgroups per unit.
+hipError_t launch_select_parts(const LayerArgs& a, int32_t n_parts, hipStream_t st, const Timing& tm);
 // Gather of every layer of a batch: per_layer = the largest per-layer gather grid.
 hipError_t launch_gather_layers(const MultiArgs& m, hipStream_t st, const Timing& tm);
 

@@ -211,12 +211,7 @@ __device__ __forceinline__ void filter_body(const LayerArgs& a, int b) {
       sure += in && kb > bin;
       mine += in && kb == bin;
     }
-    uint32_t incl = mine;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t y = __shfl_up(incl, off);
-      if (lane >= off) incl += y;
-    }
+    const uint32_t incl = wave_incl_scan(mine);
     const uint32_t wave_total = __shfl(incl, 63);
     if (wave_total) {
       uint32_t base = 0;
