@@ -251,8 +251,8 @@ __device__ __forceinline__ void copy_run(const LayerArgs& a, const SeqArgs& sq, 
   copy_rows<NT>(a, sq, g, n, [=](int64_t i) { return src0 + i; }, [=](int64_t i) { return dst0 + i; });
 }
 
-// Touch the first BYTES of the kernel arguments, one 64-byte line per lane, by
-// the first wave of the workgroup. The argument blocks are several KB that
+// Touch BYTES of the kernel arguments from byte `from` on, one 64-byte line per
+// lane, by the first wave of the workgroup. The argument blocks are 4 KB a layer, which
 // every launch finds cold, and the prologues read them field by field, each
 // read waiting for the one that decides the next. Those reads are scalar loads
 // that miss to memory one after the other; after this they find their lines in
@@ -260,7 +260,7 @@ __device__ __forceinline__ void copy_run(const LayerArgs& a, const SeqArgs& sq, 
 // 17.0 us, resolve_kernel 5.1 to 4.6 us). The returned value keeps the loads alive: pass it to args_ready() once
 // the prologue has read what it needs.
 template <int BYTES>
-__device__ __forceinline__ uint32_t args_touch() {
+__device__ __forceinline__ uint32_t args_touch(int from = 0) {
   typedef const __attribute__((address_space(4))) uint32_t* ArgPtr;
   const ArgPtr p = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
   uint32_t x = 0;
@@ -268,7 +268,7 @@ __device__ __forceinline__ uint32_t args_touch() {
 #pragma unroll
     for (int i = 0; i < (BYTES + 4095) / 4096; ++i) {
       const int at = (i * 64 + (int)threadIdx.x) * 64;
-      x |= p[(at < BYTES ? at : 0) / 4];
+      x |= p[(from + (at < BYTES ? at : 0)) / 4];
     }
   }
   return x;

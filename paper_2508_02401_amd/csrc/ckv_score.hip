@@ -486,8 +486,8 @@ __device__ __forceinline__ int layer_of(const LayersArgs& m, int b) {
 // all.
 template <int DT, int D>
 __global__ __launch_bounds__(kKpThreads) __attribute__((amdgpu_waves_per_eu(2))) void rowstats_layers_kernel(const LayersArgs m) {
-  const uint32_t touched = args_touch<sizeof(LayersArgs)>();
   const int l = layer_of(m, blockIdx.x);
+  const uint32_t touched = args_touch<sizeof(LayerArgs)>(l * (int)sizeof(LayerArgs));
   rowstats_block<DT, D>(m.lay[l], blockIdx.x - m.blk[l], touched);
 }
 
@@ -505,7 +505,6 @@ __device__ __forceinline__ void lse_merge(float& m, float& z, float m2, float z2
 // ---------------------------------------------------------------------------
 constexpr int kGroupRows = kMaxRows / 8;  // 8-row groups of one group's rows
 constexpr int kLseBatch = 16;             // partial loads in flight per thread
-constexpr int kMergeLanes = kKpThreads / kMaxRows;  // threads per row in the lse merge
 
 // QM (query-block mode, when w8 is a multiple of 32): every 32-row query
 // block belongs to one head, so a lane sums its four 8-row groups in
@@ -547,35 +546,39 @@ __device__ __forceinline__ void score_body(const LayerArgs& a, const SeqArgs& sq
   // partials while the first stages load
   float4 cv[NQ][4];
   auto merge_lse = [&] {
-    // kMergeLanes threads per row, thread j merging partials j, j + kMergeLanes,
-    // ...; their results meet in LDS in a fixed order (the gsum buffers are
-    // not in use yet)
-    float2* part = reinterpret_cast<float2*>(gsum);      // [kMergeLanes][kMaxRows]
-    float* lse_l = gsum + 2 * kMergeLanes * kMaxRows;     // [kMaxRows]
-    const int r = tid % kMaxRows, half = tid / kMaxRows;
+    // all threads share the unit's rows, padded to 32, 64 or 128: `lanes` (8, 4
+    // or 2) threads per row, thread j merging partials j, j + lanes, ...; their
+    // results meet in LDS in a fixed order (the gsum buffers are not in use
+    // yet). With two threads per row whatever the rows, half of them idled at
+    // 64 rows and each merged two batches of partials in turn (four layers of
+    // 196608 tokens in four prompts: 213 us a launch, now 204 us)
+    float2* part = reinterpret_cast<float2*>(gsum);  // [lanes][n_rows]
+    float* lse_l = gsum + 2 * kKpThreads;            // [kMaxRows]
+    const int rows_log2 = nqb == 1 ? 5 : (nqb == 2 ? 6 : 7);
+    const int n_rows = 1 << rows_log2, lanes = kKpThreads >> rows_log2;
+    const int r = tid & (n_rows - 1), lane_j = tid >> rows_log2;
     const int slot_h = r / a.w8, wrow = r - slot_h * a.w8;
     const bool valid = r < nqb * 32 && slot_h < n_sel && wrow < a.w;
     float m = -INFINITY, z = 0.f;
     if (valid && !a.lse_given) {
       const float2* pp = sq.partial + (int64_t)u * sq.n_split * kMaxRows + r;
-      for (int c0 = half; c0 < P; c0 += kMergeLanes * kLseBatch) {
+      for (int c0 = lane_j; c0 < P; c0 += lanes * kLseBatch) {
         float2 v[kLseBatch];
 #pragma unroll
         for (int u = 0; u < kLseBatch; ++u) {
-          const int c = c0 + kMergeLanes * u;
+          const int c = c0 + lanes * u;
           v[u] = c < P ? pp[(int64_t)c * kMaxRows] : make_float2(-INFINITY, 0.f);
         }
 #pragma unroll
         for (int u = 0; u < kLseBatch; ++u) lse_merge(m, z, v[u].x, v[u].y, alpha);
       }
     }
-    part[half * kMaxRows + r] = make_float2(m, z);
+    part[tid] = make_float2(m, z);
     __syncthreads();
-    if (tid < kMaxRows) {
+    if (tid < n_rows) {
       float mm = part[r].x, zz = part[r].y;
-#pragma unroll
-      for (int j = 1; j < kMergeLanes; ++j)
-        lse_merge(mm, zz, part[j * kMaxRows + r].x, part[j * kMaxRows + r].y, alpha);
+      for (int j = 1; j < lanes; ++j)
+        lse_merge(mm, zz, part[j * n_rows + r].x, part[j * n_rows + r].y, alpha);
       // padding rows: +inf, so their probabilities are 0. Caller row
       // statistics are natural logs of the scaled logits' normaliser:
       // log2(e) times that is the same quantity in exp2 units.
@@ -722,7 +725,7 @@ __device__ __forceinline__ void score_block(const LayerArgs& a, const int b, con
   // gsum[buf][r8][col]: sum over the 8 rows of 8-row group r8 of p at stage
   // column col, double-buffered by stage parity
   __shared__ __align__(16) float gsum[2 * kGroupRows * S::ST];
-  static_assert(2 * kGroupRows * S::ST >= (2 * kMergeLanes + 1) * kMaxRows, "the lse merge fits in gsum");
+  static_assert(2 * kGroupRows * S::ST >= 2 * kKpThreads + kMaxRows, "the lse merge fits in gsum");
   uint4* const slots[NS] = {slot0, slot1, slot2, slot3};
 
   const SeqArgs& sq = a.seq[find_seq(a, b, [](const SeqArgs& t) { return t.blk_kpass; })];
@@ -778,8 +781,8 @@ __global__ __launch_bounds__(kKpThreads) __attribute__((amdgpu_waves_per_eu(2)))
 // The window-sum passes of up to kLayersPerLaunch layers in one launch.
 template <int DT, int D>
 __global__ __launch_bounds__(kKpThreads) __attribute__((amdgpu_waves_per_eu(2))) void score_layers_kernel(const LayersArgs m) {
-  const uint32_t touched = args_touch<sizeof(LayersArgs)>();
   const int l = layer_of(m, blockIdx.x);
+  const uint32_t touched = args_touch<sizeof(LayerArgs)>(l * (int)sizeof(LayerArgs));
   score_block<DT, D>(m.lay[l], blockIdx.x - m.blk[l], touched);
 }
 
