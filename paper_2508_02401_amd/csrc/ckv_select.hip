@@ -19,7 +19,8 @@
 // With the layer-shared scope there is one selection per prompt (selection
 // group 0) and its rows are copied for every KV head.
 // Each step is its own launch, so stream order makes every hand-off visible
-// without device-wide fences inside the kernels.
+// without device-wide fences inside the kernels. Prompts up to kPartTokens take
+// steps 2 to 4 in one launch instead (ckv_unit.hip).
 #include <type_traits>
 
 #include "ckv_device.h"
