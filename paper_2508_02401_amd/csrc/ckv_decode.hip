@@ -528,7 +528,7 @@ void decode_kernel(const DecodeBatch B) {
     }
   }
   f32x16 o[NQ][NB];
-  float m_run[NQ], l_run[NQ];  // the maximum is of the unscaled logits
+  float m_run[NQ], l_run[NQ];  // the maximum in exp2 units
 #pragma unroll
   for (int j = 0; j < NQ; ++j) {
 #pragma unroll
@@ -573,10 +573,16 @@ void decode_kernel(const DecodeBatch B) {
 #pragma unroll
       for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[j][v]);
       mx = fmaxf(mx, __shfl_xor(mx, 32));
-      const float m_new = fmaxf(m_run[j], mx);
-      const float ms = m_new == -INFINITY ? 0.f : m_new * alpha;
+      // the scaled maximum is kept as rounded: it must be the very number that
+      // the weights below were and will be taken against, so that a row whose
+      // maximum stays is rescaled by exactly 1 when another row's moves. A
+      // product rounded anew, m * alpha inside a fused multiply-add, is off by
+      // its rounding error, the same way at every rescale: 3e-4 of the result
+      // after 256 tiles at logits up to 255
+      const float m_new = fmaxf(m_run[j], mx * alpha);
+      const float ms = m_new == -INFINITY ? 0.f : m_new;
       if (__any(m_new > m_run[j])) {  // some row's maximum moved: rescale
-        const float resc = m_run[j] == -INFINITY ? 0.f : fast_exp2(m_run[j] * alpha - ms);
+        const float resc = m_run[j] == -INFINITY ? 0.f : fast_exp2(m_run[j] - m_new);
         l_run[j] *= resc;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) o[j][nb] *= resc;
@@ -680,7 +686,7 @@ void decode_kernel(const DecodeBatch B) {
     __syncthreads();
     const float l = l_run[j] + __shfl_xor(l_run[j], 32);
     if (h == 0)
-      ml[wave][l32] = make_float2(m_run[j] == -INFINITY ? -INFINITY : m_run[j] * alpha, l);
+      ml[wave][l32] = make_float2(m_run[j], l);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
