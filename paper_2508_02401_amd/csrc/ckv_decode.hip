@@ -427,6 +427,14 @@ __device__ __forceinline__ void wait_vm() {
   asm volatile("" ::: "memory");
 }
 
+// exp2 of a logit's distance to the maximum. fp32 caches keep weights below
+// 2^-126, which the bare instruction flushes to zero; V may be that large. The
+// 16-bit types' weights are rounded to high and low parts that end sooner.
+template <int DT>
+__device__ __forceinline__ float weight_exp2(float x) {
+  return DT == 2 ? exp2f(x) : fast_exp2(x);
+}
+
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 // Up to 32 * NQ query rows. A cache row is read once, so the bound is the
@@ -582,7 +590,7 @@ void decode_kernel(const DecodeBatch B) {
       const float m_new = fmaxf(m_run[j], mx * alpha);
       const float ms = m_new == -INFINITY ? 0.f : m_new;
       if (__any(m_new > m_run[j])) {  // some row's maximum moved: rescale
-        const float resc = m_run[j] == -INFINITY ? 0.f : fast_exp2(m_run[j] - m_new);
+        const float resc = m_run[j] == -INFINITY ? 0.f : weight_exp2<DT>(m_run[j] - m_new);
         l_run[j] *= resc;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) o[j][nb] *= resc;
@@ -591,7 +599,7 @@ void decode_kernel(const DecodeBatch B) {
       float psum = 0.f;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        s[j][v] = fast_exp2(fmaf(s[j][v], alpha, -ms));
+        s[j][v] = weight_exp2<DT>(fmaf(s[j][v], alpha, -ms));
         psum += s[j][v];
       }
       l_run[j] += psum;

@@ -1,5 +1,6 @@
 """The weights of decode attention where their rounding shows: maxima that move
-often beside large ones that stay.
+often beside large ones that stay, and weights below the smallest normal fp32
+number.
 
 Logits are products of single entries (query row r holds one nonzero element),
 so they are exact and the tolerances are those of the sums alone.
@@ -58,3 +59,35 @@ def test_rows_whose_maximum_stays(dtype, G):
     err = np.abs(got[:, :, 4:] - ref[None, None, 4:]).max()
     tol = 2 * (256 + 32 + 4) * EPS + SPLIT[dtype]
     assert err <= tol, "max err %.3g, bound %.3g" % (err, tol)
+
+
+@pytest.mark.parametrize("G", [1, 40])
+@pytest.mark.parametrize("where", ["tile", "later tile"])
+def test_fp32_weights_below_the_normal_range(G, where):
+    """fp32 caches: a weight of 2^-130 of the largest still counts where V is large.
+
+    32 keys weigh 2^-130, a subnormal number with 19 bits left, with V = 2^120;
+    the keys of the largest weight have V = 0 and share the small ones' tile of
+    32, or come up to four tiles later, when the sums so far are rescaled (512 KV
+    heads keep the 160 keys in one chunk, tiles 0 and 4 with one wave)."""
+    dev, d, n_kv = torch.device("cuda:0"), 64, 512
+    n = 32 if where == "tile" else 160
+    small = slice(1, 32) if where == "tile" else slice(0, 32)
+    q = torch.zeros((1, n_kv * G, d), device=dev)
+    q[:, :, 0] = 8.0
+    k, v = torch.zeros((n, d), device=dev), torch.zeros((n, d), device=dev)
+    k[:, 0] = 130.0 * math.log(2.0)
+    k[small, 0] = 0.0
+    v[small] = 2.0 ** 120
+    kd, vd = (x.unsqueeze(0).expand(n_kv, n, d) for x in (k, v))
+    desc = ckv.attn_desc(n_kv * G, n_kv, d, torch.float32)
+    out = torch.full((1, n_kv * G, d), math.nan, device=dev)
+    ws = torch.empty(ckv.ckv_decode_workspace_bytes(desc, 1, n), dtype=torch.uint8, device=dev)
+    print("case", G, where, flush=True)
+    ckv.ckv_decode_attention(desc, q, ckv.kv_cache(kd, vd), out, ws)
+    torch.cuda.synchronize()
+    ref = float(((k[:, 0].double()).softmax(dim=0) @ v.double())[0])
+    # the exponent 130 is rounded to 2^-23 of itself in all (alpha, the maximum),
+    # 1.1e-5 of a weight, which keeps 19 bits: 1e-6
+    rel = (out.double() / ref - 1).abs().max().item()
+    assert rel <= 2e-5, "relative error %.3g" % rel
