@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include "ckv_internal.h"
+#include "ckv_plan.h"
 
 namespace {
 
@@ -758,30 +759,12 @@ int32_t decode_rows(const ckv_attn_desc* d, int32_t T) {
   return d->num_q_heads / d->num_kv_heads * T;
 }
 
-// Tokens per decode workgroup for one launch over cnt caches of n[i] tokens, the
-// same for every prompt: a multiple of one 32-key tile, at least a tile per
-// wave, and long enough that the launch is one round of workgroups, two on
-// each CU (one where the kernel's registers or LDS admit only one). A few
-// workgroups more would run after the others: 516 of them took 122 us on
-// four caches of 196608 tokens in all, where 512 are resident at once.
+// Chunk length of one launch over cnt caches of n[i] tokens: two workgroups on
+// each CU, one where the kernel's registers or LDS admit only one.
 int64_t decode_chunk_len(const ckv_attn_desc* d, int32_t max_T, int32_t cnt, const int64_t* n) {
   const bool one_per_cu = decode_rows(d, max_T) <= 64 &&
                           (d->dtype == CKV_F32 || decode_rows(d, max_T) > 32);
-  const int64_t target = one_per_cu ? ckv::kCUs : 2 * ckv::kCUs;
-  int64_t sum_n = 0, max_n = 0;
-  for (int32_t i = 0; i < cnt; ++i) {
-    sum_n += n[i];
-    max_n = n[i] > max_n ? n[i] : max_n;
-  }
-  int64_t c = ceil_div(ceil_div(sum_n * d->num_kv_heads, target), 32) * 32;
-  if (c < 128) c = 128;
-  while (c < max_n) {
-    int64_t wgs = 0;
-    for (int32_t i = 0; i < cnt; ++i) wgs += ceil_div(n[i], c) * d->num_kv_heads;
-    if (wgs <= target) break;
-    c += ceil_div(c, 32 * 32) * 32;  // about 1/32 more
-  }
-  return c;
+  return ckv::decode_chunk_len(one_per_cu ? ckv::kCUs : 2 * ckv::kCUs, d->num_kv_heads, cnt, n);
 }
 
 size_t decode_part_bytes(const ckv_attn_desc* d, int32_t T, int64_t n, int64_t chunk) {
