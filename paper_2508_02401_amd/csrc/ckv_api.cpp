@@ -759,12 +759,11 @@ int32_t decode_rows(const ckv_attn_desc* d, int32_t T) {
   return d->num_q_heads / d->num_kv_heads * T;
 }
 
-// Chunk length of one launch over cnt caches of n[i] tokens: two workgroups on
-// each CU, one where the kernel's registers or LDS admit only one.
+// Chunk length of one launch over cnt caches of n[i] tokens.
 int64_t decode_chunk_len(const ckv_attn_desc* d, int32_t max_T, int32_t cnt, const int64_t* n) {
-  const bool one_per_cu = decode_rows(d, max_T) <= 64 &&
-                          (d->dtype == CKV_F32 || decode_rows(d, max_T) > 32);
-  return ckv::decode_chunk_len(one_per_cu ? ckv::kCUs : 2 * ckv::kCUs, d->num_kv_heads, cnt, n);
+  const int64_t target =
+      ckv::kCUs * ckv::decode_wgs_per_cu(d->dtype == CKV_F32, d->head_dim, decode_rows(d, max_T));
+  return ckv::decode_chunk_len(target, d->num_kv_heads, cnt, n);
 }
 
 size_t decode_part_bytes(const ckv_attn_desc* d, int32_t T, int64_t n, int64_t chunk) {

@@ -6,6 +6,20 @@
 
 namespace ckv {
 
+// Decode workgroups per CU that a launch is cut for, by the kernel that takes
+// `rows` query rows per KV head: two, but one where the kernel's registers
+// (over 256 of a SIMD's 512) or its LDS (over 80 of 160 KB) admit no second:
+// fp32 at d = 128, 16-bit at d = 128 and fp32 with 33 to 64 rows. With 33 to 64
+// rows at d = 64 in 16 bits, and up to 32 rows at d = 64 in fp32, two would fit,
+// but one with twice the keys is as fast or faster: 2 KV heads, one cache of
+// 131072 tokens, 64 rows, 25.4 us against 28.0 (four of 65536: 38.0 against
+// 36.9); fp32, 8 rows, four of 65536: 54.9 us against 62.2.
+inline int decode_wgs_per_cu(bool f32, int head_dim, int rows) {
+  if (rows <= 32) return f32 ? 1 : 2;
+  if (rows <= 64) return 1;
+  return f32 && head_dim == 128 ? 1 : 2;
+}
+
 // Tokens per decode workgroup for one launch over cnt caches of n[i] tokens, the
 // same for every prompt: a multiple of one 32-key tile, at least a tile per
 // wave (128), for about `target` workgroups over all caches and KV heads, as

@@ -285,8 +285,8 @@ _RESOURCE_USAGE = {}
 
 def _resource_usage():
     """Per-kernel resource use of every HIP source as the compiler reports it
-    ({kernel: {"scratch": bytes/lane, "lds": bytes/block}}), compiled once per
-    session, the sources side by side."""
+    ({kernel: {"scratch": bytes/lane, "lds": bytes/block, "regs": per lane}}),
+    compiled once per session, the sources side by side."""
     import re
     import subprocess
     from paper_2508_02401_amd import build as B
@@ -307,11 +307,14 @@ def _resource_usage():
         names = re.findall(r"Function Name: (\S+)", out)
         scratch = [int(x) for x in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", out)]
         lds = [int(x) for x in re.findall(r"LDS Size \[bytes/block\]: (\d+)", out)]
+        regs = [int(v) + int(a) for v, a in
+                zip(re.findall(r" VGPRs: (\d+)", out), re.findall(r"AGPRs: (\d+)", out))]
         with open(os.path.join(B.CSRC, src)) as f:
             has_kernels = "__global__" in f.read()
-        assert len(names) == len(scratch) == len(lds) and bool(names) == has_kernels, src
-        for n, sc, l in zip(names, scratch, lds):
-            _RESOURCE_USAGE[n] = {"scratch": sc, "lds": l, "src": src}
+        assert len(names) == len(scratch) == len(lds) == len(regs), src
+        assert bool(names) == has_kernels, src
+        for n, sc, l, r in zip(names, scratch, lds, regs):
+            _RESOURCE_USAGE[n] = {"scratch": sc, "lds": l, "regs": r, "src": src}
     return _RESOURCE_USAGE
 
 

@@ -7,6 +7,7 @@ import subprocess
 import pytest
 
 from paper_2508_02401_amd import build as B
+from tests.test_abi_cpu import _resource_usage
 
 SHIM = r"""
 #include "ckv_plan.h"
@@ -14,6 +15,7 @@ extern "C" {
 int64_t chunk_len(int64_t target, int64_t n_kv, int32_t cnt, const int64_t* n) {
   return ckv::decode_chunk_len(target, n_kv, cnt, n);
 }
+int per_cu(int f32, int d, int rows) { return ckv::decode_wgs_per_cu(f32 != 0, d, rows); }
 }
 """
 
@@ -67,3 +69,20 @@ def test_decode_chunks_are_balanced_and_one_round_where_they_can_be(plan, target
         # one round whenever twice the even share is surely enough for it
         if units <= target // 2 - 16 and even > 1024:
             assert wgs <= target, (n_kv, lens, c)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dt", [0, 1, 2])
+def test_decode_is_cut_for_workgroups_that_the_kernels_admit(plan, dt, d):
+    # workgroups of 4 waves, one on each SIMD: 512 registers a lane to share out
+    # in eights, and 160 KB of LDS a CU
+    usage = _resource_usage()
+    for rows in (1, 32, 33, 64, 65, 128):
+        kernel = ("13decode_kernelILi%dELi%dELi%dE" % (dt, d, 1 if rows <= 32 else 2) if rows <= 64 else
+                  "decode_rows_kernel_%sILi%dELi%dE" % ("f32" if dt == 2 else "16", dt, d))
+        u = [v for k, v in usage.items() if kernel in k]
+        assert len(u) == 1, kernel
+        admit = min(512 // (-(-u[0]["regs"] // 8) * 8), 160 * 1024 // u[0]["lds"], 2)
+        # cut for one workgroup of longer chunks although two fit: measured faster
+        longer = d == 64 and (dt == 2 and rows <= 32 or dt != 2 and 32 < rows <= 64)
+        assert plan.per_cu(dt == 2, d, rows) == (1 if longer else admit), (kernel, u[0])
