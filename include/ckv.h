@@ -342,8 +342,9 @@ size_t ckv_decode_batch_workspace_bytes(const ckv_attn_desc *desc, const ckv_dec
 /* Decode attention of every prompt of seqs[0..num_seqs). The host array is
  * read during the call only; queries, caches and outputs are device memory
  * owned by the caller. The prompts go to the GPU in launches of up to 24
- * (one decode and one merge kernel each), their workgroups sized from the
- * launch's total cache length. Validates every prompt before any launch;
+ * (one decode and one merge kernel each; prompts of up to 64 query rows per KV
+ * head go apart from those of more when their caches are long), their
+ * workgroups sized from the launch's total cache length. Validates every prompt before any launch;
  * CKV_ERR_INVALID_ARG / CKV_ERR_UNSUPPORTED as ckv_decode_attention,
  * CKV_ERR_WORKSPACE when the workspace is short. Asynchronous on stream. */
 int ckv_decode_attention_batch(const ckv_attn_desc *desc, const ckv_decode_seq *seqs,

@@ -827,23 +827,51 @@ int check_decode_seq(const ckv_attn_desc* d, const ckv_decode_seq* s) {
   return CKV_OK;
 }
 
+// Whether T query tokens have no more rows per KV head than decode_kernel takes.
+// It can also write out the result of a prompt of one chunk.
+bool decode_few_rows(const ckv_attn_desc* d, int32_t T) { return decode_rows(d, T) <= 64; }
+
 // A batch goes to the GPU in runs of at most kMaxDecodeSeqs consecutive
-// prompts, one launch each: the size of the run that starts at i0, and its
-// chunk length.
+// prompts, each of them one launch, or two when some of its prompts have few
+// rows, others have many, and two launches are faster (decode_split_pays).
+struct DecodeLaunch {
+  bool few;                          // all its prompts have few rows
+  int32_t cnt;                       // how many prompts
+  int32_t at[ckv::kMaxDecodeSeqs];   // and which
+  int64_t chunk;                     // cached tokens per workgroup
+};
 int32_t decode_run(int32_t i0, int32_t num_seqs) {
   return num_seqs - i0 < ckv::kMaxDecodeSeqs ? num_seqs - i0 : ckv::kMaxDecodeSeqs;
 }
-int32_t decode_run_T(const ckv_decode_seq* seqs, int32_t i0, int32_t cnt) {
-  int32_t T = 0;
-  for (int32_t i = i0; i < i0 + cnt; ++i) T = seqs[i].T > T ? seqs[i].T : T;
-  return T;
+// The launches of the prompts i0 .. i0 + cnt - 1; returns how many.
+int32_t decode_launches(const ckv_attn_desc* d, const ckv_decode_seq* seqs, int32_t i0, int32_t cnt,
+                        DecodeLaunch* out) {
+  int64_t few_keys = 0;
+  for (int32_t i = i0; i < i0 + cnt; ++i)
+    if (decode_few_rows(d, seqs[i].T)) few_keys += seqs[i].cache.n * d->num_kv_heads;
+  const bool split = ckv::decode_split_pays(d->dtype == CKV_F32, few_keys);
+  int32_t launches = 0;
+  for (const bool few : {true, false}) {
+    DecodeLaunch& r = out[launches];
+    r.few = true;
+    r.cnt = 0;
+    int64_t n[ckv::kMaxDecodeSeqs];
+    int32_t T = 0;
+    for (int32_t i = i0; i < i0 + cnt; ++i) {
+      const bool is_few = decode_few_rows(d, seqs[i].T);
+      if (split ? is_few != few : !few) continue;
+      r.few = r.few && is_few;
+      T = seqs[i].T > T ? seqs[i].T : T;
+      n[r.cnt] = seqs[i].cache.n;
+      r.at[r.cnt++] = i;
+    }
+    if (r.cnt == 0) continue;
+    r.chunk = decode_chunk_len(d, T, r.cnt, n);
+    ++launches;
+  }
+  return launches;
 }
-int64_t decode_run_chunk(const ckv_attn_desc* d, const ckv_decode_seq* seqs, int32_t i0,
-                         int32_t cnt) {
-  int64_t n[ckv::kMaxDecodeSeqs];
-  for (int32_t i = 0; i < cnt; ++i) n[i] = seqs[i0 + i].cache.n;
-  return decode_chunk_len(d, decode_run_T(seqs, i0, cnt), cnt, n);
-}
+
 // Chunk length of a launch over one cache, or over a full and a compact one.
 int64_t decode_chunk_one(const ckv_attn_desc* d, int32_t T, int64_t n) {
   return decode_chunk_len(d, T, 1, &n);
@@ -852,10 +880,6 @@ int64_t decode_chunk_two(const ckv_attn_desc* d, int32_t T, int64_t n0, int64_t 
   const int64_t n[2] = {n0, n1};
   return decode_chunk_len(d, T, 2, n);
 }
-// Whether a launch whose largest prompt has T query tokens runs the kernel that
-// can write a one-chunk prompt's result.
-bool decode_direct(const ckv_attn_desc* d, int32_t T) { return decode_rows(d, T) <= 64; }
-
 }  // namespace
 
 size_t ckv_decode_workspace_bytes(const ckv_attn_desc* desc, int32_t T, int64_t n) {
@@ -877,7 +901,7 @@ int ckv_decode_attention(const ckv_attn_desc* desc, const void* q, int64_t q_str
   ckv::DecodeBatch b;
   decode_batch_init(desc, b);
   decode_batch_add(desc, q, q_stride_t, q_stride_h, T, cache, out, static_cast<float*>(workspace),
-                   decode_chunk_one(desc, T, cache->n), decode_direct(desc, T), b);
+                   decode_chunk_one(desc, T, cache->n), decode_few_rows(desc, T), b);
   const hipError_t e = ckv::launch_decode(desc->dtype, b, (hipStream_t)stream);
   return e == hipSuccess ? CKV_OK : hip_fail(e);
 }
@@ -889,10 +913,13 @@ size_t ckv_decode_batch_workspace_bytes(const ckv_attn_desc* desc, const ckv_dec
     if (check_decode_seq(desc, &seqs[i]) != CKV_OK) return 0;
   size_t total = 0;
   for (int32_t i0 = 0; i0 < num_seqs; i0 += ckv::kMaxDecodeSeqs) {
-    const int32_t cnt = decode_run(i0, num_seqs);
-    const int64_t chunk = decode_run_chunk(desc, seqs, i0, cnt);
-    for (int32_t i = i0; i < i0 + cnt; ++i)
-      total += decode_part_bytes(desc, seqs[i].T, seqs[i].cache.n, chunk);
+    DecodeLaunch run[2];
+    const int32_t launches = decode_launches(desc, seqs, i0, decode_run(i0, num_seqs), run);
+    for (int32_t l = 0; l < launches; ++l) {
+      const DecodeLaunch& r = run[l];
+      for (int32_t j = 0; j < r.cnt; ++j)
+        total += decode_part_bytes(desc, seqs[r.at[j]].T, seqs[r.at[j]].cache.n, r.chunk);
+    }
   }
   return total;
 }
@@ -910,19 +937,21 @@ int ckv_decode_attention_batch(const ckv_attn_desc* desc, const ckv_decode_seq* 
     return CKV_ERR_WORKSPACE;
   char* part = static_cast<char*>(workspace);
   for (int32_t i0 = 0; i0 < num_seqs; i0 += ckv::kMaxDecodeSeqs) {
-    const int32_t cnt = decode_run(i0, num_seqs);
-    const int64_t chunk = decode_run_chunk(desc, seqs, i0, cnt);
-    ckv::DecodeBatch b;
-    decode_batch_init(desc, b);
-    const bool direct = decode_direct(desc, decode_run_T(seqs, i0, cnt));
-    for (int32_t i = i0; i < i0 + cnt; ++i) {
-      const ckv_decode_seq& s = seqs[i];
-      decode_batch_add(desc, s.q, s.q_stride_t, s.q_stride_h, s.T, &s.cache, s.out,
-                       reinterpret_cast<float*>(part), chunk, direct, b);
-      part += decode_part_bytes(desc, s.T, s.cache.n, chunk);
+    DecodeLaunch run[2];
+    const int32_t launches = decode_launches(desc, seqs, i0, decode_run(i0, num_seqs), run);
+    for (int32_t l = 0; l < launches; ++l) {
+      const DecodeLaunch& r = run[l];
+      ckv::DecodeBatch b;
+      decode_batch_init(desc, b);
+      for (int32_t j = 0; j < r.cnt; ++j) {
+        const ckv_decode_seq& s = seqs[r.at[j]];
+        decode_batch_add(desc, s.q, s.q_stride_t, s.q_stride_h, s.T, &s.cache, s.out,
+                         reinterpret_cast<float*>(part), r.chunk, r.few, b);
+        part += decode_part_bytes(desc, s.T, s.cache.n, r.chunk);
+      }
+      const hipError_t err = ckv::launch_decode(desc->dtype, b, (hipStream_t)stream);
+      if (err != hipSuccess) return hip_fail(err);
     }
-    const hipError_t err = ckv::launch_decode(desc->dtype, b, (hipStream_t)stream);
-    if (err != hipSuccess) return hip_fail(err);
   }
   return CKV_OK;
 }
@@ -977,9 +1006,9 @@ int ckv_layer_error(const ckv_attn_desc* desc, const void* q, int64_t q_stride_t
   ckv::DecodeBatch db;
   decode_batch_init(desc, db);
   decode_batch_add(desc, q, q_stride_t, q_stride_h, T, full, a_full, reinterpret_cast<float*>(part),
-                   chunk, decode_direct(desc, T), db);
+                   chunk, decode_few_rows(desc, T), db);
   decode_batch_add(desc, q, q_stride_t, q_stride_h, T, comp, a_comp,
-                   reinterpret_cast<float*>(part + pa), chunk, decode_direct(desc, T), db);
+                   reinterpret_cast<float*>(part + pa), chunk, decode_few_rows(desc, T), db);
   hipError_t err;
   if ((err = ckv::launch_decode(desc->dtype, db, st)) != hipSuccess) return hip_fail(err);
   ckv::ErrorArgs ea;

@@ -50,4 +50,16 @@ inline int64_t decode_chunk_len(int64_t target, int64_t n_kv, int32_t cnt, const
   return even;
 }
 
+// Whether the prompts with at most 64 query rows of a batch that also has prompts
+// with more are launched apart, given their cached tokens times KV heads. The
+// kernel for more rows gives a prompt one wave per 32 rows, so a one-token
+// prompt there leaves three of four waves idle, but a launch pair of its own
+// costs about 9 us. 16 bits, 15 one-token caches beside one of 300 tokens with
+// 112 rows, 4 KV heads: 246000 keys 39.7 us together and 41.5 apart, 492000 keys
+// 64.9 and 60.6; the fp32 kernel's waves are slower: 31000 keys 36 and 51, 61000
+// keys 61 and 58, 123000 keys 99 and 69.
+inline bool decode_split_pays(bool f32, int64_t few_keys) {
+  return few_keys >= (f32 ? 1 << 16 : 1 << 18);
+}
+
 }  // namespace ckv

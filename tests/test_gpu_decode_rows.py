@@ -52,3 +52,33 @@ def test_decode_rows_and_lengths(dtype, d, G, T):
                         for t in range(q.shape[0])])
         err = np.abs(out.cpu().numpy() - ref)
         assert np.all(err <= 1e-4 * (np.abs(ref) + 1.0)), "n %d: max err %.3g" % (n, err.max())
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_few_rows_keep_their_kernel_beside_many(dtype):
+    """A batch of one-token prompts and of prompts of more than 64 query rows per KV
+    head, the former with 2 * 150000 keys, enough to be launched apart: each kind is
+    launched as it is without the other, so the results are the same bit for bit."""
+    dev, n_kv, G, d = torch.device("cuda:0"), 2, 7, 128
+    H = n_kv * G
+    gen = torch.Generator(device=dev).manual_seed(3)
+    desc = ckv.attn_desc(H, n_kv, d, dtype)
+    prompts = []
+    for n, T in [(700, 1), (3000, 16), (129, 1), (5000, 10), (150000, 1)]:
+        q = (torch.randn((T, H, d), generator=gen, device=dev) * 1.5).to(dtype)
+        k, v = (torch.randn((n_kv, n, d), generator=gen, device=dev).to(dtype) for _ in range(2))
+        prompts.append((q, k, v))
+
+    def run(some):
+        outs = [torch.full(q.shape, math.nan, device=dev) for q, _, _ in some]
+        seqs = [ckv.decode_seq(q, ckv.kv_cache(k, v), o) for (q, k, v), o in zip(some, outs)]
+        ws = torch.empty(ckv.ckv_decode_batch_workspace_bytes(desc, seqs), dtype=torch.uint8, device=dev)
+        ckv.ckv_decode_attention_batch(desc, seqs, ws)
+        torch.cuda.synchronize()
+        return outs
+
+    print("case", dtype, flush=True)
+    both = run(prompts)
+    for which in ([0, 2, 4], [1, 3]):
+        for i, o in zip(which, run([prompts[i] for i in which])):
+            assert torch.equal(both[i], o), i
