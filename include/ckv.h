@@ -308,7 +308,8 @@ typedef struct {
 } ckv_kv_cache;
 
 /* Workspace of ckv_decode_attention for T query tokens over n cached tokens
- * (0 on invalid input). */
+ * (0 on invalid input). It holds for fewer tokens and shorter caches too, so a
+ * program may size its buffer once for its largest T and n. */
 size_t ckv_decode_workspace_bytes(const ckv_attn_desc *desc, int32_t T, int64_t n);
 
 /* out[t][h][:] (fp32, [T][H][d] contiguous) = softmax over the n cached keys
@@ -335,7 +336,8 @@ typedef struct {
   float *out;             /* [T][H][d] fp32, contiguous */
 } ckv_decode_seq;
 
-/* Workspace of ckv_decode_attention_batch (0 on invalid input). */
+/* Workspace of ckv_decode_attention_batch (0 on invalid input). It holds for
+ * the same number of prompts with fewer tokens or shorter caches too. */
 size_t ckv_decode_batch_workspace_bytes(const ckv_attn_desc *desc, const ckv_decode_seq *seqs,
                                         int32_t num_seqs);
 
@@ -351,7 +353,8 @@ int ckv_decode_attention_batch(const ckv_attn_desc *desc, const ckv_decode_seq *
                                int32_t num_seqs, void *workspace, size_t workspace_bytes,
                                void *stream);
 
-/* Workspace of ckv_layer_error (0 on invalid input). */
+/* Workspace of ckv_layer_error (0 on invalid input). It holds for a smaller T,
+ * n_full, n_comp or D too. */
 size_t ckv_layer_error_workspace_bytes(const ckv_attn_desc *desc, int32_t T, int64_t n_full,
                                        int64_t n_comp, int32_t D);
 

@@ -771,6 +771,18 @@ size_t decode_part_bytes(const ckv_attn_desc* d, int32_t T, int64_t n, int64_t c
                   (d->head_dim + 2) * sizeof(float));
 }
 
+// Bytes that hold the partials of cnt caches of n[i] tokens and up to T query
+// tokens, and of shorter caches and fewer tokens. mixed: the prompts may differ
+// in their tokens.
+size_t decode_bound_bytes(const ckv_attn_desc* d, int32_t T, int32_t cnt, const int64_t* n, bool mixed) {
+  int64_t tiles = 0;
+  for (int32_t i = 0; i < cnt; ++i) tiles += ceil_div(n[i], 128);
+  const int64_t rows = ckv::decode_partial_rows(d->dtype == CKV_F32, d->head_dim, ckv::kCUs,
+                                                d->num_kv_heads, cnt, tiles, decode_rows(d, T), mixed);
+  // every prompt's part is rounded up
+  return align_up((size_t)rows * (d->head_dim + 2) * sizeof(float)) + (size_t)(cnt - 1) * kAlign;
+}
+
 void decode_batch_init(const ckv_attn_desc* d, ckv::DecodeBatch& b) {
   b.n = 0;
   b.H = d->num_q_heads;
@@ -880,11 +892,34 @@ int64_t decode_chunk_two(const ckv_attn_desc* d, int32_t T, int64_t n0, int64_t 
   const int64_t n[2] = {n0, n1};
   return decode_chunk_len(d, T, 2, n);
 }
+// ckv_layer_error's workspace beside the partials of its two decodes.
+size_t error_fixed_bytes(const ckv_attn_desc* d, int32_t T, int32_t D) {
+  const size_t outs = align_up((size_t)T * d->num_q_heads * d->head_dim * sizeof(float));
+  const size_t proj = align_up((size_t)(ceil_div(D, 32) + 1) * 2 * T * sizeof(float));
+  const int64_t K = (int64_t)d->num_q_heads * d->head_dim;
+  return 2 * outs + proj + proj_tiles_bytes(D, T, K) + proj_split_bytes(T, K);
+}
+
+// Bytes of partials that a batch uses.
+size_t decode_batch_bytes(const ckv_attn_desc* d, const ckv_decode_seq* seqs, int32_t num_seqs) {
+  size_t total = 0;
+  DecodeLaunch run[2];
+  for (int32_t i0 = 0; i0 < num_seqs; i0 += ckv::kMaxDecodeSeqs) {
+    const int32_t launches = decode_launches(d, seqs, i0, decode_run(i0, num_seqs), run);
+    for (int32_t l = 0; l < launches; ++l)
+      for (int32_t j = 0; j < run[l].cnt; ++j) {
+        const ckv_decode_seq& s = seqs[run[l].at[j]];
+        total += decode_part_bytes(d, s.T, s.cache.n, run[l].chunk);
+      }
+  }
+  return total;
+}
+
 }  // namespace
 
 size_t ckv_decode_workspace_bytes(const ckv_attn_desc* desc, int32_t T, int64_t n) {
   if (check_attn(desc, T) != CKV_OK || n < 1 || n >= ((int64_t)1 << 31)) return 0;
-  return decode_part_bytes(desc, T, n, decode_chunk_one(desc, T, n));
+  return decode_bound_bytes(desc, T, 1, &n, false);
 }
 
 int ckv_decode_attention(const ckv_attn_desc* desc, const void* q, int64_t q_stride_t,
@@ -895,13 +930,15 @@ int ckv_decode_attention(const ckv_attn_desc* desc, const void* q, int64_t q_str
   if ((rc = check_q(desc, q, q_stride_t, q_stride_h, T)) != CKV_OK) return rc;
   if ((rc = check_cache(desc, cache)) != CKV_OK) return rc;
   if (!out || ((uintptr_t)out & 3u)) return CKV_ERR_INVALID_ARG;
+  // what this call uses; the size functions add room for smaller calls
+  const int64_t chunk = decode_chunk_one(desc, T, cache->n);
   if (!workspace || !aligned16(workspace) ||
-      workspace_bytes < ckv_decode_workspace_bytes(desc, T, cache->n))
+      workspace_bytes < decode_part_bytes(desc, T, cache->n, chunk))
     return CKV_ERR_WORKSPACE;
   ckv::DecodeBatch b;
   decode_batch_init(desc, b);
   decode_batch_add(desc, q, q_stride_t, q_stride_h, T, cache, out, static_cast<float*>(workspace),
-                   decode_chunk_one(desc, T, cache->n), decode_few_rows(desc, T), b);
+                   chunk, decode_few_rows(desc, T), b);
   const hipError_t e = ckv::launch_decode(desc->dtype, b, (hipStream_t)stream);
   return e == hipSuccess ? CKV_OK : hip_fail(e);
 }
@@ -913,13 +950,14 @@ size_t ckv_decode_batch_workspace_bytes(const ckv_attn_desc* desc, const ckv_dec
     if (check_decode_seq(desc, &seqs[i]) != CKV_OK) return 0;
   size_t total = 0;
   for (int32_t i0 = 0; i0 < num_seqs; i0 += ckv::kMaxDecodeSeqs) {
-    DecodeLaunch run[2];
-    const int32_t launches = decode_launches(desc, seqs, i0, decode_run(i0, num_seqs), run);
-    for (int32_t l = 0; l < launches; ++l) {
-      const DecodeLaunch& r = run[l];
-      for (int32_t j = 0; j < r.cnt; ++j)
-        total += decode_part_bytes(desc, seqs[r.at[j]].T, seqs[r.at[j]].cache.n, r.chunk);
+    const int32_t cnt = decode_run(i0, num_seqs);
+    int64_t n[ckv::kMaxDecodeSeqs];
+    int32_t T = 0;
+    for (int32_t i = 0; i < cnt; ++i) {
+      n[i] = seqs[i0 + i].cache.n;
+      T = seqs[i0 + i].T > T ? seqs[i0 + i].T : T;
     }
+    total += decode_bound_bytes(desc, T, cnt, n, cnt > 1);
   }
   return total;
 }
@@ -933,7 +971,7 @@ int ckv_decode_attention_batch(const ckv_attn_desc* desc, const ckv_decode_seq* 
     if (rc != CKV_OK) return rc;
   }
   if (!workspace || !aligned16(workspace) ||
-      workspace_bytes < ckv_decode_batch_workspace_bytes(desc, seqs, num_seqs))
+      workspace_bytes < decode_batch_bytes(desc, seqs, num_seqs))
     return CKV_ERR_WORKSPACE;
   char* part = static_cast<char*>(workspace);
   for (int32_t i0 = 0; i0 < num_seqs; i0 += ckv::kMaxDecodeSeqs) {
@@ -961,14 +999,8 @@ size_t ckv_layer_error_workspace_bytes(const ckv_attn_desc* desc, int32_t T, int
   if (check_attn(desc, T) != CKV_OK || D < 1 || n_full < 1 || n_comp < 1 ||
       n_full >= ((int64_t)1 << 31) || n_comp >= ((int64_t)1 << 31))
     return 0;
-  const size_t outs = align_up((size_t)T * desc->num_q_heads * desc->head_dim * sizeof(float));
-  const int64_t chunk = decode_chunk_two(desc, T, n_full, n_comp);
-  const size_t parts = decode_part_bytes(desc, T, n_full, chunk) + decode_part_bytes(desc, T, n_comp, chunk);
-  const size_t proj = align_up((size_t)(ceil_div(D, 32) + 1) * 2 * T * sizeof(float));
-  const int64_t K = (int64_t)desc->num_q_heads * desc->head_dim;
-  const size_t proj_y = proj_tiles_bytes(D, T, K);
-  const size_t x_hl = proj_split_bytes(T, K);
-  return 2 * outs + parts + proj + proj_y + x_hl;
+  const int64_t n[2] = {n_full, n_comp};
+  return error_fixed_bytes(desc, T, D) + decode_bound_bytes(desc, T, 2, n, false);
 }
 
 int ckv_layer_error(const ckv_attn_desc* desc, const void* q, int64_t q_stride_t,
@@ -987,18 +1019,18 @@ int ckv_layer_error(const ckv_attn_desc* desc, const void* q, int64_t q_stride_t
     return CKV_ERR_INVALID_ARG;
   if (!(eps >= 0.f) || isinf(eps)) return CKV_ERR_INVALID_ARG;
   if (!ratio || !e || ((uintptr_t)ratio & 3u) || ((uintptr_t)e & 3u)) return CKV_ERR_INVALID_ARG;
+  // both decodes in one batch: the full cache and the compressed one
+  const int64_t chunk = decode_chunk_two(desc, T, full->n, comp->n);
+  const size_t pa = decode_part_bytes(desc, T, full->n, chunk);
+  const size_t pb = decode_part_bytes(desc, T, comp->n, chunk);
   if (!workspace || !aligned16(workspace) ||
-      workspace_bytes < ckv_layer_error_workspace_bytes(desc, T, full->n, comp->n, D))
+      workspace_bytes < error_fixed_bytes(desc, T, D) + pa + pb)
     return CKV_ERR_WORKSPACE;
   char* ws = static_cast<char*>(workspace);
   const size_t outs = align_up((size_t)T * K * sizeof(float));
   float* a_full = reinterpret_cast<float*>(ws);
   float* a_comp = reinterpret_cast<float*>(ws + outs);
   char* part = ws + 2 * outs;
-  // both decodes in one batch: the full cache and the compressed one
-  const int64_t chunk = decode_chunk_two(desc, T, full->n, comp->n);
-  const size_t pa = decode_part_bytes(desc, T, full->n, chunk);
-  const size_t pb = decode_part_bytes(desc, T, comp->n, chunk);
   float* proj = reinterpret_cast<float*>(part + pa + pb);
   float* proj_y = reinterpret_cast<float*>(
       reinterpret_cast<char*>(proj) + align_up((size_t)(ceil_div(D, 32) + 1) * 2 * T * sizeof(float)));

@@ -50,6 +50,30 @@ inline int64_t decode_chunk_len(int64_t target, int64_t n_kv, int32_t cnt, const
   return even;
 }
 
+// Most partial rows (chunks of a KV head times its query rows) that the launches
+// over cnt caches can need, for these row counts and cache lengths or smaller
+// ones: rows is the largest prompt's, tiles the sum over the caches of
+// ceil(n / 128). A launch has at most one chunk per 128 keys, and at most its even
+// share's count plus one per cache and head. Fewer rows may mean more chunks (the
+// 32-row kernel is cut for twice the workgroups of the 64-row one) and, in a mixed
+// batch, two launches; a size that grew with neither would refuse a program
+// that sizes its buffer once, for its longest caches and most tokens.
+inline int64_t decode_partial_rows(bool f32, int head_dim, int64_t cus, int64_t n_kv, int32_t cnt,
+                                   int64_t tiles, int64_t rows, bool mixed) {
+  auto most = [&](int64_t r) {  // of one launch whose largest prompt has r rows
+    const int64_t by_share = cus * decode_wgs_per_cu(f32, head_dim, (int)r) + cnt * n_kv;
+    return (tiles * n_kv < by_share ? tiles * n_kv : by_share) * r;
+  };
+  int64_t few = most(rows < 32 ? rows : 32);
+  if (rows > 32) {
+    const int64_t f = most(rows < 64 ? rows : 64);
+    few = f > few ? f : few;
+  }
+  if (rows <= 64) return few;
+  const int64_t many = most(rows);
+  return mixed ? few + many : (few > many ? few : many);
+}
+
 // Whether the prompts with at most 64 query rows of a batch that also has prompts
 // with more are launched apart, given their cached tokens times KV heads. The
 // kernel for more rows gives a prompt one wave per 32 rows, so a one-token

@@ -5,7 +5,9 @@ import random
 import subprocess
 
 import pytest
+import torch
 
+import paper_2508_02401_amd as ckv
 from paper_2508_02401_amd import build as B
 from tests.test_abi_cpu import _resource_usage
 
@@ -86,3 +88,64 @@ def test_decode_is_cut_for_workgroups_that_the_kernels_admit(plan, dt, d):
         # cut for one workgroup of longer chunks although two fit: measured faster
         longer = d == 64 and (dt == 2 and rows <= 32 or dt != 2 and 32 < rows <= 64)
         assert plan.per_cu(dt == 2, d, rows) == (1 if longer else admit), (kernel, u[0])
+
+
+# ---- decode workspace sizes: bounds for smaller calls too ------------------
+DTYPES = {0: torch.bfloat16, 1: torch.float16, 2: torch.float32}
+SHAPES = [(0, 32, 8, 128), (2, 32, 8, 128), (1, 16, 2, 64), (2, 16, 2, 64), (0, 32, 32, 128), (0, 7, 1, 64)]
+
+
+def _seq(T, n, d):
+    """A prompt whose addresses are never touched: only its sizes are read."""
+    s = ckv.ckv_decode_seq()
+    s.q, s.q_stride_t, s.q_stride_h, s.T, s.out = 1 << 20, 1 << 16, d, T, 1 << 20
+    c = s.cache
+    c.k, c.v, c.stride_head, c.stride_tok, c.n = 1 << 20, 1 << 20, n * d, d, n
+    return s
+
+
+def _need(plan, dt, H, n_kv, d, prompts):
+    """Bytes of partials that a batch of (T, n) uses, in one launch."""
+    G = H // n_kv
+    rows = max(T for T, _ in prompts) * G
+    c = _chunk(plan, 256 * plan.per_cu(dt == 2, d, rows), n_kv, [n for _, n in prompts])
+    up = lambda x: -(-x // 256) * 256
+    return sum(up(n_kv * -(-n // c) * T * G * (d + 2) * 4) for T, n in prompts)
+
+
+@pytest.mark.parametrize("dt,H,n_kv,d", SHAPES)
+def test_decode_workspace_grows_with_tokens_and_cache(plan, dt, H, n_kv, d):
+    desc = ckv.attn_desc(H, n_kv, d, DTYPES[dt])
+    lens = [1, 31, 128, 129, 700, 8192, 8193, 20000, 65536, 65537, 131072, 1000003]
+    tokens = [T for T in list(range(1, 19)) + [31, 32, 64, 128] if T * H // n_kv <= 128]
+    size = [[ckv.ckv_decode_workspace_bytes(desc, T, n) for n in lens] for T in tokens]
+    err = [[ckv.ckv_layer_error_workspace_bytes(desc, T, n, max(n // 7, 1), 512) for n in lens]
+           for T in tokens]
+    for a in (size, err):
+        for row in a:
+            assert row == sorted(row)
+        for col in zip(*a):
+            assert list(col) == sorted(col)
+    for T, row in zip(tokens, size):
+        for n, got in zip(lens, row):
+            assert got >= _need(plan, dt, H, n_kv, d, [(T, n)]), (T, n)
+
+
+@pytest.mark.parametrize("dt,H,n_kv,d", SHAPES)
+def test_decode_batch_workspace_holds_for_smaller_prompts(plan, dt, H, n_kv, d):
+    desc = ckv.attn_desc(H, n_kv, d, DTYPES[dt])
+    rng = random.Random(H + dt)
+    few = lambda T: T * H // n_kv <= 64
+    for _ in range(60):
+        cnt = rng.choice([1, 2, 5, 24])
+        top = 128 * n_kv // H
+        big = [(rng.randint(1, top), int(200000 ** rng.random())) for _ in range(cnt)]
+        size = ckv.ckv_decode_batch_workspace_bytes(desc, [_seq(T, n, d) for T, n in big])
+        for _ in range(20):
+            small = [(rng.randint(1, T), rng.randint(1, n)) for T, n in big]
+            assert ckv.ckv_decode_batch_workspace_bytes(
+                desc, [_seq(T, n, d) for T, n in small]) <= size, (big, small)
+            # together, or the prompts of few rows apart
+            a, b = [p for p in small if few(p[0])], [p for p in small if not few(p[0])]
+            assert _need(plan, dt, H, n_kv, d, small) <= size
+            assert sum(_need(plan, dt, H, n_kv, d, x) for x in (a, b) if x) <= size, (big, small)
