@@ -333,22 +333,25 @@ int run_score(const ckv_layer_desc* d, const ckv::LayerArgs& a, hipStream_t st) 
   return rc != CKV_OK ? rc : run_pool(a, st);
 }
 
-// Parts per selection unit of one layer, or 0 when a prompt is too long for
-// every part to read its scores (kPartTokens). The parts of all units together are one round
-// of workgroups (the unit kernel's LDS admits one per CU), each with at least
-// kPartRows rows to copy; without copies there is nothing to share out.
-int32_t unit_parts(const ckv::LayerArgs& a) {
-  int64_t rows = 1;
+// Whether one launch takes a layer's selection from the thresholds to the copied
+// rows, and its workgroups per unit. Not when a prompt is too long for every part
+// to read its scores (kPartTokens), and not when units past the CUs leave none to
+// split the units with most rows: a part then copies far more than an even share
+// (over four times it, and over kUnitCopyRows), where the ranges of the compact
+// launch share the rows out. 16 prompts of 16 KV heads, 15 of them with 1024
+// tokens, one with 65536 tokens and 4096 rows a head: 158 us, 128 with the three
+// launches; 32 KV heads: 469 and 424. With 8 KV heads, 8192 rows, the long
+// prompt's units get 13 parts each: 130 and 133 us.
+bool unit_parts(const ckv::LayerArgs& a, ckv::UnitParts& p) {
+  int64_t rows[ckv::kMaxSeqs], total = 0;
   for (int32_t i = 0; i < a.num_seqs; ++i) {
     const ckv::SeqArgs& q = a.seq[i];
-    if (q.L - a.tail > (a.do_gather ? ckv::kPartTokens : ckv::kPartTokensNoCopy)) return 0;
-    const int64_t r = (int64_t)q.n_ret * (a.shared ? a.n_kv : 1);
-    rows = r > rows ? r : rows;
+    if (q.L - a.tail > (a.do_gather ? ckv::kPartTokens : ckv::kPartTokensNoCopy)) return false;
+    rows[i] = a.do_gather ? (int64_t)q.n_ret * (a.shared ? a.n_kv : 1) : 1;
+    total += rows[i] * a.n_sg;
   }
-  if (!a.do_gather) return 1;
-  const int64_t most = ckv::kCUs / (a.num_seqs * a.n_sg), useful = ceil_div(rows, ckv::kPartRows);
-  const int64_t n = most < useful ? most : useful;
-  return n < 1 ? 1 : (int32_t)n;
+  const int64_t most = ckv::deal_unit_parts(ckv::kCUs, a.num_seqs, a.n_sg, rows, p);
+  return most <= ckv::kUnitCopyRows || most <= 4 * ceil_div(total, ckv::kCUs);
 }
 
 // Selection on scores already in place. With caller scores (ckv_select) the
@@ -365,8 +368,8 @@ int run_select(const ckv::LayerArgs& a, bool caller_scores, hipStream_t st) {
       return hip_fail(e);
     if ((e = ckv::launch_hist(a, gs, st, none)) != hipSuccess) return hip_fail(e);
   }
-  const int32_t parts = unit_parts(a);
-  if (parts > 0) {
+  ckv::UnitParts parts;
+  if (unit_parts(a, parts)) {
     ckv::Timing tm = timing(ckv::kStageSelect, !caller_scores, false);
     tm.stop = timing(ckv::kStageGather, false, true).stop;
     e = ckv::launch_select_parts(a, parts, st, tm);

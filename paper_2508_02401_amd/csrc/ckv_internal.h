@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "ckv.h"
+#include "ckv_plan.h"
 
 namespace ckv {
 
@@ -41,7 +42,6 @@ constexpr int kUnitCopyRows = 512;
 constexpr int64_t kUnitTokens = 131072;
 constexpr int64_t kPartTokens = 65536;
 constexpr int64_t kPartTokensNoCopy = 32768;
-constexpr int kPartRows = 16;      // kept rows per part of a split selection unit (at least)
 constexpr int kHistBits = 12;      // first-level histogram: key bits 30..19
 constexpr int kHistBins = 1 << kHistBits;
 constexpr int kHistShift = 31 - kHistBits;
@@ -281,8 +281,8 @@ hipError_t launch_decode(int dtype, const DecodeBatch& b, hipStream_t st);
 hipError_t launch_stream_gather(const LayerArgs& a, int32_t sinks, int grid, hipStream_t st);
 hipError_t launch_error(int w_dtype, const ErrorArgs& a, hipStream_t st);
 hipError_t launch_select_units(const MultiArgs& m, hipStream_t st, const Timing& tm);
-// The same for one layer, n_parts workgroups per unit.
-hipError_t launch_select_parts(const LayerArgs& a, int32_t n_parts, hipStream_t st, const Timing& tm);
+// The same for one layer, every unit split into parts.
+hipError_t launch_select_parts(const LayerArgs& a, const UnitParts& p, hipStream_t st, const Timing& tm);
 // Gather of every layer of a batch: per_layer = the largest per-layer gather grid.
 hipError_t launch_gather_layers(const MultiArgs& m, hipStream_t st, const Timing& tm);
 

@@ -86,4 +86,37 @@ inline bool decode_split_pays(bool f32, int64_t few_keys) {
   return few_keys >= (f32 ? 1 << 16 : 1 << 18);
 }
 
+// Workgroups of one layer's selection units when each unit is split into parts
+// that copy a share of its kept rows: prompt s's units (n_sg of them) have
+// parts(s) workgroups each, unit after unit from first[s] on.
+constexpr int kPlanSeqs = 16;  // most prompts of a layer call
+constexpr int kPartRows = 16;  // kept rows per part (at least, where a unit has so many)
+struct UnitParts {
+  int32_t first[kPlanSeqs + 1];
+  int32_t n_sg;
+};
+
+// Deals one round of workgroups (cus of them, the unit kernel's LDS admits one
+// per CU) out over the units, one to each and the others by the rows that a unit
+// keeps, rows[s] for each unit of prompt s; units past cus run in further rounds,
+// unsplit. Returns the most rows of a part. The same count for every unit made a
+// long prompt's parts the last to end: 16 prompts of 8 KV heads, one keeping 8192
+// rows a head and the others 128, took 187 us, now 130.
+inline int64_t deal_unit_parts(int64_t cus, int32_t num_seqs, int32_t n_sg, const int64_t* rows,
+                               UnitParts& p) {
+  const int64_t units = (int64_t)num_seqs * n_sg, more = cus > units ? cus - units : 0;
+  int64_t total = 0, most = 0;
+  for (int32_t s = 0; s < num_seqs; ++s) total += rows[s] * n_sg;
+  p.n_sg = n_sg;
+  p.first[0] = 0;
+  for (int32_t s = 0; s < num_seqs; ++s) {
+    const int64_t share = 1 + more * rows[s] / total, useful = rows[s] / kPartRows;
+    const int64_t n = share < useful ? share : (useful > 1 ? useful : 1);
+    p.first[s + 1] = p.first[s] + (int32_t)(n * n_sg);
+    const int64_t r = (rows[s] + n - 1) / n;
+    most = r > most ? r : most;
+  }
+  return most;
+}
+
 }  // namespace ckv

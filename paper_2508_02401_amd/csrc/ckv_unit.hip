@@ -499,11 +499,15 @@ __global__ __launch_bounds__(kUT) void select_unit_kernel(const MultiArgs m) {
 // 20 and 32 us. Two prompts of 24571 and 9001 tokens that share one selection
 // for 8 heads had all copies made by the few ranges holding kept tokens: 58
 // us, now 18 us.
-__global__ __launch_bounds__(kUT) void select_parts_kernel(const LayerArgs a, int32_t n_parts) {
+__global__ __launch_bounds__(kUT) void select_parts_kernel(const LayerArgs a, const UnitParts p) {
   __shared__ UnitLds sm;
-  args_ready(args_touch<sizeof(LayerArgs)>());
-  const int u = blockIdx.x / n_parts;
-  unit_body(a, u, blockIdx.x - u * n_parts, n_parts, a.do_gather != 0, sm);
+  args_ready(args_touch<sizeof(LayerArgs) + sizeof(UnitParts)>());
+  const int b = blockIdx.x;
+  int s = 0;
+  while (s + 1 < a.num_seqs && b >= p.first[s + 1]) ++s;
+  const int n_parts = (p.first[s + 1] - p.first[s]) / p.n_sg;
+  const int g = (b - p.first[s]) / n_parts;
+  unit_body(a, s * a.n_sg + g, b - p.first[s] - g * n_parts, n_parts, a.do_gather != 0, sm);
 }
 
 }  // namespace
@@ -512,11 +516,10 @@ hipError_t launch_select_units(const MultiArgs& m, hipStream_t st, const Timing&
   return launch(select_unit_kernel, m.n_layers * m.per_layer, kUT, st, tm, m);
 }
 
-hipError_t launch_select_parts(const LayerArgs& a, int32_t n_parts, hipStream_t st, const Timing& tm) {
-  void* args[] = {const_cast<LayerArgs*>(&a), &n_parts};
+hipError_t launch_select_parts(const LayerArgs& a, const UnitParts& p, hipStream_t st, const Timing& tm) {
+  void* args[] = {const_cast<LayerArgs*>(&a), const_cast<UnitParts*>(&p)};
   return hipExtLaunchKernel(reinterpret_cast<const void*>(select_parts_kernel),
-                            dim3(a.num_seqs * a.n_sg * n_parts), dim3(kUT), args, 0, st, tm.start,
-                            tm.stop, 0);
+                            dim3(p.first[a.num_seqs]), dim3(kUT), args, 0, st, tm.start, tm.stop, 0);
 }
 
 }  // namespace ckv

@@ -62,30 +62,55 @@ def test_select_exact(Ls, values):
 @pytest.mark.parametrize("L,budgets", [(77, (9, 76, 77)), (2100, (40, 700)), (16500, (333, 16499)),
                                        (65540, (1000,)), (65600, (1000,))])
 def test_compress_layer_parts(L, budgets, keep_window, shared):
-    dev, H, n_kv, d, w = torch.device("cuda:0"), 12, 3, 64, 8
-    gen = torch.Generator(device=dev).manual_seed(L)
+    _compress_and_check(12, 3, [(L, b) for b in budgets], keep_window, shared)
+
+
+# Batches of prompts, most of them short, with budgets at both ends of their range:
+# units whose parts differ in number (8 KV heads: one prompt keeps most of the
+# batch's rows) and more units than CUs (24 KV heads), with like and unlike rows.
+RAGGED = {
+    "parts": (8, 8, [(30001, 14000)] + [(200 + 31 * i, 9 + 40 * i) for i in range(13)] + [(77, 77), (500, 8)]),
+    "rounds": (24, 24, [(2100, 8), (2100, 9), (2100, 2099), (2100, 2100), (300, 40), (5000, 600),
+                        (77, 76), (900, 1000), (1025, 8), (64, 30), (333, 333), (2047, 12)]),
+    "uneven": (24, 24, [(40000, 3000)] + [(300, 20)] * 11),
+}
+
+
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("keep_window", [True, False])
+@pytest.mark.parametrize("batch", sorted(RAGGED))
+def test_compress_layer_ragged(batch, keep_window, shared):
+    H, n_kv, prompts = RAGGED[batch]
+    _compress_and_check(H, n_kv, prompts, keep_window, shared)
+
+
+def _compress_and_check(H, n_kv, prompts, keep_window, shared):
+    """One layer call over prompts (L, budget) against a stable sort of its scores."""
+    dev, d, w = torch.device("cuda:0"), 64, 8
+    gen = torch.Generator(device=dev).manual_seed(prompts[0][0])
+    L = max(n for n, _ in prompts)
     q = torch.randn((H, w, d), generator=gen, device=dev).to(torch.float16)
     k, v = (torch.randn((n_kv, L, d), generator=gen, device=dev).to(torch.float16) for _ in range(2))
     flags = (ckv.CKV_KEEP_WINDOW if keep_window else 0) | (ckv.CKV_SHARE_LAYER if shared else 0)
     desc = ckv.layer_desc(H, n_kv, d, w, torch.float16, 0.0, ckv.CKV_POOL_MAX, 7, flags)
-    mask = np.array([1, 0, 0, 1] * 3, np.uint8)
+    mask = np.array([1] + [0] * (H // n_kv - 2) + [1] * (H > n_kv), np.uint8)
+    mask = np.tile(mask, n_kv)
     tail = w if keep_window else 0
     seqs = []
-    for b in budgets:  # one call, so that prompts and parts mix
-        s = ckv.alloc_outputs(desc, ckv.Seq(q, k, v, b))
-        s.scores = torch.empty((1 if shared else n_kv, L - tail), device=dev)
-        if s.scores.data_ptr() % 16 == 0:
-            seqs.append(s)
-    print("case", L, budgets, keep_window, shared, flush=True)
+    for n, b in prompts:  # one call, so that prompts and parts mix
+        s = ckv.alloc_outputs(desc, ckv.Seq(q, k[:, L - n:], v[:, L - n:], b))
+        s.scores = torch.empty((1 if shared else n_kv, n - tail), device=dev)
+        seqs.append(s)
+    print("case", H, prompts, keep_window, shared, flush=True)
     ckv.ckv_compress_layer(desc, mask, seqs, ckv.alloc_workspace(desc, seqs, dev))
     torch.cuda.synchronize()
-    for b, s in zip(budgets, seqs):
+    for (n, b), s in zip(prompts, seqs):
         sc, idx = s.scores.cpu().numpy(), s.idx.cpu().numpy().reshape(1 if shared else n_kv, -1)
         for g in range(n_kv):
             r = 0 if shared else g
-            n = min(b, L)
-            want = np.arange(L) if n == L else np.concatenate([_top(sc[r], n - tail),
-                                                               np.arange(L - tail, L)])
-            assert np.array_equal(idx[r], want)
+            kept = min(b, n)
+            want = np.arange(n) if kept == n else np.concatenate([_top(sc[r], kept - tail),
+                                                                  np.arange(n - tail, n)])
+            assert np.array_equal(idx[r], want), (n, b, g)
             at = torch.from_numpy(want).to(dev)
-            assert torch.equal(s.k_out[g], k[g, at]) and torch.equal(s.v_out[g], v[g, at])
+            assert torch.equal(s.k_out[g], s.k[g, at]) and torch.equal(s.v_out[g], s.v[g, at]), (n, b, g)

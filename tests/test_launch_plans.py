@@ -17,6 +17,12 @@ extern "C" {
 int64_t chunk_len(int64_t target, int64_t n_kv, int32_t cnt, const int64_t* n) {
   return ckv::decode_chunk_len(target, n_kv, cnt, n);
 }
+int64_t deal(int64_t cus, int32_t n, int32_t n_sg, const int64_t* rows, int32_t* first) {
+  ckv::UnitParts p;
+  const int64_t most = ckv::deal_unit_parts(cus, n, n_sg, rows, p);
+  for (int32_t s = 0; s <= n; ++s) first[s] = p.first[s];
+  return most;
+}
 int per_cu(int f32, int d, int rows) { return ckv::decode_wgs_per_cu(f32 != 0, d, rows); }
 }
 """
@@ -33,6 +39,9 @@ def plan(tmp_path_factory):
     so.chunk_len.restype = ctypes.c_int64
     so.chunk_len.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int32,
                              ctypes.POINTER(ctypes.c_int64)]
+    so.deal.restype = ctypes.c_int64
+    so.deal.argtypes = [ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.POINTER(ctypes.c_int64),
+                        ctypes.POINTER(ctypes.c_int32)]
     return so
 
 
@@ -88,6 +97,38 @@ def test_decode_is_cut_for_workgroups_that_the_kernels_admit(plan, dt, d):
         # cut for one workgroup of longer chunks although two fit: measured faster
         longer = d == 64 and (dt == 2 and rows <= 32 or dt != 2 and 32 < rows <= 64)
         assert plan.per_cu(dt == 2, d, rows) == (1 if longer else admit), (kernel, u[0])
+
+
+# ---- parts of selection units ------------------------------------------------
+def _layers():
+    yield 8, [8192] + [128] * 15
+    yield 8, [16384] + [128] * 15
+    yield 16, [4096] + [128] * 15
+    yield 64, [512] * 16
+    yield 1, [1]
+    yield 8, [2048]
+    yield 3, [17, 1, 16]
+    rng = random.Random(7)
+    for _ in range(400):
+        yield rng.choice([1, 2, 3, 4, 8, 16, 32, 64]), [
+            int(rng.choice([40, 3000, 65536, 1 << 30]) ** rng.random()) for _ in range(rng.randint(1, 16))]
+
+
+def test_unit_parts_are_one_round_dealt_out_by_rows(plan):
+    for n_sg, rows in _layers():
+        n = len(rows)
+        first = (ctypes.c_int32 * (n + 1))()
+        most = plan.deal(256, n, n_sg, (ctypes.c_int64 * n)(*rows), first)
+        parts = [(b - a) // n_sg for a, b in zip(first, first[1:])]
+        assert first[0] == 0 and all((b - a) % n_sg == 0 for a, b in zip(first, first[1:]))
+        assert min(parts) >= 1 and first[n] <= max(256, n * n_sg), (n_sg, rows, parts)
+        assert most == max(-(-r // p) for r, p in zip(rows, parts))
+        assert all(p == 1 or r // p >= 16 for r, p in zip(rows, parts)), (n_sg, rows, parts)
+        # the workgroups past one per unit are shared out by rows
+        even = sum(rows) * n_sg / max(256 - n * n_sg, 1)
+        assert most <= max(31, even + 1) or n * n_sg >= 256, (n_sg, rows, parts)
+        if len(set(rows)) == 1 and n * n_sg <= 256 and rows[0] >= 16 * 256:
+            assert parts[0] == 256 // (n * n_sg)
 
 
 # ---- decode workspace sizes: bounds for smaller calls too ------------------
