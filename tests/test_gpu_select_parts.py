@@ -65,14 +65,17 @@ def test_compress_layer_parts(L, budgets, keep_window, shared):
     _compress_and_check(12, 3, [(L, b) for b in budgets], keep_window, shared)
 
 
-# Batches of prompts, most of them short, with budgets at both ends of their range:
-# units whose parts differ in number (8 KV heads: one prompt keeps most of the
-# batch's rows) and more units than CUs (24 KV heads), with like and unlike rows.
+# A batch of prompts of which one or two are long, with budgets at both ends of
+# their range: units whose parts differ in number (8 KV heads: one prompt keeps
+# most of the batch's rows), more units than CUs (24 KV heads), and prompts past
+# 65536 scored tokens, which send the whole batch through the three launches.
 RAGGED = {
     "parts": (8, 8, [(30001, 14000)] + [(200 + 31 * i, 9 + 40 * i) for i in range(13)] + [(77, 77), (500, 8)]),
     "rounds": (24, 24, [(2100, 8), (2100, 9), (2100, 2099), (2100, 2100), (300, 40), (5000, 600),
                         (77, 76), (900, 1000), (1025, 8), (64, 30), (333, 333), (2047, 12)]),
     "uneven": (24, 24, [(40000, 3000)] + [(300, 20)] * 11),
+    "long": (12, 3, [(65700, 8), (300, 9), (65700, 65699), (300, 8), (300, 300), (2100, 700)]),
+    "long keep all": (12, 3, [(65700, 65700), (300, 299), (70001, 9), (9000, 9001), (65700, 33000)]),
 }
 
 
