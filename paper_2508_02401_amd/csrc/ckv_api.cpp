@@ -343,14 +343,17 @@ int run_score(const ckv_layer_desc* d, const ckv::LayerArgs& a, hipStream_t st) 
 // launches; 32 KV heads: 469 and 424. With 8 KV heads, 8192 rows, the long
 // prompt's units get 13 parts each: 130 and 133 us.
 bool unit_parts(const ckv::LayerArgs& a, ckv::UnitParts& p) {
-  int64_t rows[ckv::kMaxSeqs], total = 0;
+  const int32_t heads = a.shared && a.do_gather ? a.n_kv : 1;  // whose rows a unit copies
+  int64_t rows[ckv::kMaxSeqs], total = 0, longest = 0;
   for (int32_t i = 0; i < a.num_seqs; ++i) {
     const ckv::SeqArgs& q = a.seq[i];
     if (q.L - a.tail > (a.do_gather ? ckv::kPartTokens : ckv::kPartTokensNoCopy)) return false;
-    rows[i] = a.do_gather ? (int64_t)q.n_ret * (a.shared ? a.n_kv : 1) : 1;
-    total += rows[i] * a.n_sg;
+    rows[i] = a.do_gather ? q.n_ret : 1;
+    total += rows[i] * a.n_sg * heads;
+    longest = q.L - a.tail > longest ? q.L - a.tail : longest;
   }
-  const int64_t most = ckv::deal_unit_parts(ckv::kCUs, a.num_seqs, a.n_sg, rows, p);
+  const int64_t round = ckv::part_round(ckv::kCUs, total, longest);
+  const int64_t most = ckv::deal_unit_parts(round, a.num_seqs, a.n_sg, heads, rows, p);
   return most <= ckv::kUnitCopyRows || most <= 4 * ceil_div(total, ckv::kCUs);
 }
 

@@ -87,33 +87,52 @@ inline bool decode_split_pays(bool f32, int64_t few_keys) {
 }
 
 // Workgroups of one layer's selection units when each unit is split into parts
-// that copy a share of its kept rows: prompt s's units (n_sg of them) have
-// parts(s) workgroups each, unit after unit from first[s] on.
+// that copy a share of its kept rows: prompt s's units have parts[s] workgroups
+// each, unit after unit from first[s] on.
 constexpr int kPlanSeqs = 16;  // most prompts of a layer call
 constexpr int kPartRows = 16;  // kept rows per part (at least, where a unit has so many)
 struct UnitParts {
   int32_t first[kPlanSeqs + 1];
-  int32_t n_sg;
+  int32_t parts[kPlanSeqs];
 };
 
-// Deals one round of workgroups (cus of them, the unit kernel's LDS admits one
-// per CU) out over the units, one to each and the others by the rows that a unit
-// keeps, rows[s] for each unit of prompt s; units past cus run in further rounds,
-// unsplit. Returns the most rows of a part. The same count for every unit made a
+// Workgroups that the parts of a layer call may be, for its kept rows in all and
+// its longest prompt's scored tokens: one round (a unit workgroup's LDS fills a
+// CU) when the prompts are short or a part of half a round would copy more than
+// 256 rows, else half a round. The other half is what a caller's other streams
+// run on meanwhile: layers of 32768 tokens, 2048 kept by each of 8 heads, over
+// four streams took 49.6 us each with a whole round, 43.4 with half, over two
+// 50.7 and 47.6; on one stream 61.0 and 61.4. Short prompts' K passes leave CUs
+// free by themselves: 4013 tokens on one stream took 42.0 us with a round, 42.7
+// with half. With 32768 of 65000 tokens kept the copies count: 128 and 145 us.
+constexpr int64_t kPartShort = 8192;
+inline int64_t part_round(int64_t cus, int64_t total_rows, int64_t scored) {
+  return scored < kPartShort || total_rows > cus / 2 * 256 ? cus : cus / 2;
+}
+
+// Deals a round of `cus` workgroups out over the units, one to each and the others
+// by the rows that a unit keeps, rows[s] of each head and unit of prompt s; units
+// past cus run in further rounds, unsplit. A unit that copies for several heads
+// (a shared selection) gets a multiple of them where it gets as many, so that no
+// part ends one head's rows and starts another's, two turns in a row (two prompts
+// of 24571 and 9001 tokens, 8 heads: 52.1 us with parts over head ends, 50.5
+// without). Returns the most rows of a part. The same count for every unit made a
 // long prompt's parts the last to end: 16 prompts of 8 KV heads, one keeping 8192
 // rows a head and the others 128, took 187 us, now 130.
-inline int64_t deal_unit_parts(int64_t cus, int32_t num_seqs, int32_t n_sg, const int64_t* rows,
-                               UnitParts& p) {
+inline int64_t deal_unit_parts(int64_t cus, int32_t num_seqs, int32_t n_sg, int32_t heads,
+                               const int64_t* rows, UnitParts& p) {
   const int64_t units = (int64_t)num_seqs * n_sg, more = cus > units ? cus - units : 0;
   int64_t total = 0, most = 0;
   for (int32_t s = 0; s < num_seqs; ++s) total += rows[s] * n_sg;
-  p.n_sg = n_sg;
   p.first[0] = 0;
   for (int32_t s = 0; s < num_seqs; ++s) {
-    const int64_t share = 1 + more * rows[s] / total, useful = rows[s] / kPartRows;
-    const int64_t n = share < useful ? share : (useful > 1 ? useful : 1);
-    p.first[s + 1] = p.first[s] + (int32_t)(n * n_sg);
-    const int64_t r = (rows[s] + n - 1) / n;
+    const int64_t unit_rows = rows[s] * heads;
+    const int64_t share = 1 + more * rows[s] / total, useful = unit_rows / kPartRows;
+    int64_t n = share < useful ? share : (useful > 1 ? useful : 1);
+    if (n > heads) n -= n % heads;
+    p.parts[s] = (int32_t)n;
+    p.first[s + 1] = p.first[s] + p.parts[s] * n_sg;
+    const int64_t r = (unit_rows + n - 1) / n;
     most = r > most ? r : most;
   }
   return most;

@@ -308,12 +308,11 @@ __device__ __forceinline__ uint32_t token_of_rank(const UnitLds& sm, const uint3
   return t;
 }
 
-// Part `part` of n_parts of selection unit u: the unit's output rows, KV head by
-// KV head when the selection is shared, are dealt out in consecutive shares.
-__device__ __forceinline__ void unit_body(const LayerArgs& a, int u, int part, int n_parts,
+// Part `part` of n_parts of prompt s's selection unit g: the unit's output rows, KV
+// head by KV head when the selection is shared, are dealt out in consecutive shares.
+__device__ __forceinline__ void unit_body(const LayerArgs& a, int s, int g, int part, int n_parts,
                                           bool copy, UnitLds& sm) {
   const int tid = threadIdx.x;
-  const int s = u / a.n_sg, g = u - s * a.n_sg;
   const SeqArgs& sq = a.seq[s];
   const int64_t Ls = sq.L - a.tail;
   const int n_ret = sq.n_ret;
@@ -490,7 +489,9 @@ __device__ __forceinline__ void unit_body(const LayerArgs& a, int u, int part, i
 __global__ __launch_bounds__(kUT) void select_unit_kernel(const MultiArgs m) {
   __shared__ UnitLds sm;
   const int l = blockIdx.x / m.per_layer;
-  unit_body(layer_args(m, l), blockIdx.x - l * m.per_layer, 0, 1, m.unit_copy != 0, sm);
+  const LayerArgs& a = layer_args(m, l);
+  const int u = blockIdx.x - l * m.per_layer, s = u / a.n_sg;
+  unit_body(a, s, u - s * a.n_sg, 0, 1, m.unit_copy != 0, sm);
 }
 
 // One layer: n_parts workgroups per unit. Bound by its chain of dependent steps
@@ -505,9 +506,8 @@ __global__ __launch_bounds__(kUT) void select_parts_kernel(const LayerArgs a, co
   const int b = blockIdx.x;
   int s = 0;
   while (s + 1 < a.num_seqs && b >= p.first[s + 1]) ++s;
-  const int n_parts = (p.first[s + 1] - p.first[s]) / p.n_sg;
-  const int g = (b - p.first[s]) / n_parts;
-  unit_body(a, s * a.n_sg + g, b - p.first[s] - g * n_parts, n_parts, a.do_gather != 0, sm);
+  const int at = b - p.first[s], g = at / p.parts[s];
+  unit_body(a, s, g, at - g * p.parts[s], p.parts[s], a.do_gather != 0, sm);
 }
 
 }  // namespace

@@ -374,9 +374,11 @@ def test_selection_kernels_fit_beside_two_k_pass_workgroups():
     # A caller that runs layers on several streams can overlap one layer's
     # selection kernels with another layer's K passes: each of those kernels
     # must fit in the LDS that two K-pass
-    # workgroups leave free on a CU (160 KB). The stack's one-workgroup-per-
-    # group selection kernel is not among them (it holds a 131072-token
-    # segment's bitmaps in LDS and waits for CUs to drain).
+    # workgroups leave free on a CU (160 KB). The unit kernels are not among them
+    # (they hold a 131072-token segment's bitmaps in LDS and wait for CUs to
+    # drain): select_unit_kernel of the stack and select_parts_kernel, which takes
+    # the selection of layers up to 65536 scored tokens and so keeps to half of
+    # the CUs unless it has many rows to copy.
     usage = _resource_usage()
     lds = {k: u["lds"] for k, u in usage.items()}
     # the K-pass kernels of 16-bit d = 128 layers (the Llama / Qwen shapes)

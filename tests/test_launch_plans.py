@@ -17,11 +17,14 @@ extern "C" {
 int64_t chunk_len(int64_t target, int64_t n_kv, int32_t cnt, const int64_t* n) {
   return ckv::decode_chunk_len(target, n_kv, cnt, n);
 }
-int64_t deal(int64_t cus, int32_t n, int32_t n_sg, const int64_t* rows, int32_t* first) {
+int64_t deal(int64_t cus, int32_t n, int32_t n_sg, int32_t heads, const int64_t* rows, int32_t* first) {
   ckv::UnitParts p;
-  const int64_t most = ckv::deal_unit_parts(cus, n, n_sg, rows, p);
+  const int64_t most = ckv::deal_unit_parts(cus, n, n_sg, heads, rows, p);
   for (int32_t s = 0; s <= n; ++s) first[s] = p.first[s];
   return most;
+}
+int64_t part_round(int64_t cus, int64_t rows, int64_t scored) {
+  return ckv::part_round(cus, rows, scored);
 }
 int per_cu(int f32, int d, int rows) { return ckv::decode_wgs_per_cu(f32 != 0, d, rows); }
 }
@@ -39,8 +42,10 @@ def plan(tmp_path_factory):
     so.chunk_len.restype = ctypes.c_int64
     so.chunk_len.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int32,
                              ctypes.POINTER(ctypes.c_int64)]
+    so.part_round.restype = ctypes.c_int64
+    so.part_round.argtypes = [ctypes.c_int64] * 3
     so.deal.restype = ctypes.c_int64
-    so.deal.argtypes = [ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.POINTER(ctypes.c_int64),
+    so.deal.argtypes = [ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.POINTER(ctypes.c_int64),
                         ctypes.POINTER(ctypes.c_int32)]
     return so
 
@@ -114,21 +119,48 @@ def _layers():
             int(rng.choice([40, 3000, 65536, 1 << 30]) ** rng.random()) for _ in range(rng.randint(1, 16))]
 
 
+def _deal(plan, n_sg, heads, rows):
+    n = len(rows)
+    first = (ctypes.c_int32 * (n + 1))()
+    most = plan.deal(256, n, n_sg, heads, (ctypes.c_int64 * n)(*rows), first)
+    assert first[0] == 0 and all((b - a) % n_sg == 0 for a, b in zip(first, first[1:]))
+    return most, [(b - a) // n_sg for a, b in zip(first, first[1:])]
+
+
 def test_unit_parts_are_one_round_dealt_out_by_rows(plan):
     for n_sg, rows in _layers():
-        n = len(rows)
-        first = (ctypes.c_int32 * (n + 1))()
-        most = plan.deal(256, n, n_sg, (ctypes.c_int64 * n)(*rows), first)
-        parts = [(b - a) // n_sg for a, b in zip(first, first[1:])]
-        assert first[0] == 0 and all((b - a) % n_sg == 0 for a, b in zip(first, first[1:]))
-        assert min(parts) >= 1 and first[n] <= max(256, n * n_sg), (n_sg, rows, parts)
+        units = len(rows) * n_sg
+        most, parts = _deal(plan, n_sg, 1, rows)
+        assert min(parts) >= 1 and sum(parts) * n_sg <= max(256, units), (n_sg, rows, parts)
         assert most == max(-(-r // p) for r, p in zip(rows, parts))
         assert all(p == 1 or r // p >= 16 for r, p in zip(rows, parts)), (n_sg, rows, parts)
         # the workgroups past one per unit are shared out by rows
-        even = sum(rows) * n_sg / max(256 - n * n_sg, 1)
-        assert most <= max(31, even + 1) or n * n_sg >= 256, (n_sg, rows, parts)
-        if len(set(rows)) == 1 and n * n_sg <= 256 and rows[0] >= 16 * 256:
-            assert parts[0] == 256 // (n * n_sg)
+        even = sum(rows) * n_sg / max(256 - units, 1)
+        assert most <= max(31, even + 1) or units >= 256, (n_sg, rows, parts)
+        if len(set(rows)) == 1 and units <= 256 and rows[0] >= 16 * 256:
+            assert parts[0] == 256 // units
+
+
+def test_unit_parts_of_a_shared_selection_keep_to_one_head(plan):
+    for heads, rows in _layers():
+        most, parts = _deal(plan, 1, heads, rows)
+        assert sum(parts) <= 256
+        for r, p in zip(rows, parts):
+            assert p <= heads or p % heads == 0, (heads, rows, parts)
+            assert p == 1 or r * heads // p >= 16
+        assert most == max(-(-r * heads // p) for r, p in zip(rows, parts))
+
+
+def test_unit_parts_leave_half_the_cus_unless_rows_are_many(plan):
+    # a part's LDS leaves no room for another layer's K-pass workgroup on its CU
+    usage = _resource_usage()
+    lds = {k: u["lds"] for k, u in usage.items()}
+    parts = max(v for k, v in lds.items() if "select_parts_kernel" in k)
+    kpass = min(v for k, v in lds.items() if "rowstats_kernel" in k or "score_kernel" in k)
+    assert parts + kpass > 160 * 1024
+    assert plan.part_round(256, 1, 8192) == plan.part_round(256, 8 * 4096, 65536) == 128
+    # many rows to copy, or short prompts, whose K passes leave CUs free
+    assert plan.part_round(256, 8 * 4096 + 1, 65536) == plan.part_round(256, 1, 8191) == 256
 
 
 # ---- decode workspace sizes: bounds for smaller calls too ------------------
