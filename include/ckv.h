@@ -386,7 +386,10 @@ int ckv_last_hip_error(void);
  * the launches). Stages: 0 row statistics (K pass 1), 1 window sums (K pass
  * 2; the small merge kernel between the passes is not covered), 2 pooling,
  * head mean and histogram, 3 selection (threshold search), 4 compaction and
- * gather. Arrays are hipEvent_t[CKV_NUM_STAGES] owned by the caller, created
+ * gather. Where one launch takes a layer from the thresholds to the copied rows
+ * (only up to 65536 scored tokens, 32768 in ckv_select), stage 3 covers it, stage
+ * 4's two events are recorded on the stream right behind it, so every pair is
+ * valid after any call and begin[3] to end[4] is selection and gather. Arrays are hipEvent_t[CKV_NUM_STAGES] owned by the caller, created
  * with timing enabled; a NULL entry leaves that stage untimed (each timed
  * launch costs a few microseconds of dispatch overlap); pass NULL arrays to
  * stop. Per host thread. */

@@ -373,9 +373,11 @@ int run_select(const ckv::LayerArgs& a, bool caller_scores, hipStream_t st) {
   }
   ckv::UnitParts parts;
   if (unit_parts(a, parts)) {
-    ckv::Timing tm = timing(ckv::kStageSelect, !caller_scores, false);
-    tm.stop = timing(ckv::kStageGather, false, true).stop;
-    e = ckv::launch_select_parts(a, parts, st, tm);
+    e = ckv::launch_select_parts(a, parts, st, timing(ckv::kStageSelect, !caller_scores, true));
+    // the launch counts as stage 3; stage 4's events close behind it
+    const ckv::Timing behind = timing(ckv::kStageGather, true, true);
+    if (e == hipSuccess && behind.start) e = hipEventRecord(behind.start, st);
+    if (e == hipSuccess && behind.stop) e = hipEventRecord(behind.stop, st);
     return e == hipSuccess ? CKV_OK : hip_fail(e);
   }
   if ((e = ckv::launch_filter(a, gs, st, timing(ckv::kStageSelect, !caller_scores, false))) !=
