@@ -504,10 +504,19 @@ __global__ __launch_bounds__(kUT) void select_parts_kernel(const LayerArgs a, co
   __shared__ UnitLds sm;
   args_ready(args_touch<sizeof(LayerArgs) + sizeof(UnitParts)>());
   const int b = blockIdx.x;
-  int s = 0;
-  while (s + 1 < a.num_seqs && b >= p.first[s + 1]) ++s;
-  const int at = b - p.first[s], g = at / p.parts[s];
-  unit_body(a, s, g, at - g * p.parts[s], p.parts[s], a.do_gather != 0, sm);
+  int s = 0, u, part, parts = p.same;  // part of unit u of prompt s
+  if (parts > 0) {
+    u = b / parts;
+    part = b - u * parts;
+    s = u / a.n_sg;
+    u -= s * a.n_sg;
+  } else {
+    while (s + 1 < a.num_seqs && b >= p.first[s + 1]) ++s;
+    parts = p.parts[s];
+    u = (b - p.first[s]) / parts;
+    part = b - p.first[s] - u * parts;
+  }
+  unit_body(a, s, u, part, parts, a.do_gather != 0, sm);
 }
 
 }  // namespace

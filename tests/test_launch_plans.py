@@ -17,10 +17,12 @@ extern "C" {
 int64_t chunk_len(int64_t target, int64_t n_kv, int32_t cnt, const int64_t* n) {
   return ckv::decode_chunk_len(target, n_kv, cnt, n);
 }
-int64_t deal(int64_t cus, int32_t n, int32_t n_sg, int32_t heads, const int64_t* rows, int32_t* first) {
+int64_t deal(int64_t cus, int32_t n, int32_t n_sg, int32_t heads, const int64_t* rows, int32_t* first,
+             int32_t* same) {
   ckv::UnitParts p;
   const int64_t most = ckv::deal_unit_parts(cus, n, n_sg, heads, rows, p);
   for (int32_t s = 0; s <= n; ++s) first[s] = p.first[s];
+  *same = p.same;
   return most;
 }
 int64_t part_round(int64_t cus, int64_t rows, int64_t scored) {
@@ -46,7 +48,7 @@ def plan(tmp_path_factory):
     so.part_round.argtypes = [ctypes.c_int64] * 3
     so.deal.restype = ctypes.c_int64
     so.deal.argtypes = [ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.POINTER(ctypes.c_int64),
-                        ctypes.POINTER(ctypes.c_int32)]
+                        ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]
     return so
 
 
@@ -121,10 +123,12 @@ def _layers():
 
 def _deal(plan, n_sg, heads, rows):
     n = len(rows)
-    first = (ctypes.c_int32 * (n + 1))()
-    most = plan.deal(256, n, n_sg, heads, (ctypes.c_int64 * n)(*rows), first)
+    first, same = (ctypes.c_int32 * (n + 1))(), ctypes.c_int32()
+    most = plan.deal(256, n, n_sg, heads, (ctypes.c_int64 * n)(*rows), first, ctypes.byref(same))
     assert first[0] == 0 and all((b - a) % n_sg == 0 for a, b in zip(first, first[1:]))
-    return most, [(b - a) // n_sg for a, b in zip(first, first[1:])]
+    parts = [(b - a) // n_sg for a, b in zip(first, first[1:])]
+    assert same.value == (parts[0] if len(set(parts)) == 1 else 0)
+    return most, parts
 
 
 def test_unit_parts_are_one_round_dealt_out_by_rows(plan):
