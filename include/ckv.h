@@ -346,9 +346,10 @@ size_t ckv_decode_batch_workspace_bytes(const ckv_attn_desc *desc, const ckv_dec
  * owned by the caller. The prompts go to the GPU in launches of up to 24
  * (one decode and one merge kernel each; prompts of up to 64 query rows per KV
  * head go apart from those of more when their caches are long), their
- * workgroups sized from the launch's total cache length. Validates every prompt before any launch;
- * CKV_ERR_INVALID_ARG / CKV_ERR_UNSUPPORTED as ckv_decode_attention,
- * CKV_ERR_WORKSPACE when the workspace is short. Asynchronous on stream. */
+ * workgroups sized from the launch's total cache length. Validates every
+ * prompt before any launch; CKV_ERR_INVALID_ARG / CKV_ERR_UNSUPPORTED as
+ * ckv_decode_attention, CKV_ERR_WORKSPACE when the workspace is short.
+ * Asynchronous on stream. */
 int ckv_decode_attention_batch(const ckv_attn_desc *desc, const ckv_decode_seq *seqs,
                                int32_t num_seqs, void *workspace, size_t workspace_bytes,
                                void *stream);
@@ -386,13 +387,14 @@ int ckv_last_hip_error(void);
  * the launches). Stages: 0 row statistics (K pass 1), 1 window sums (K pass
  * 2; the small merge kernel between the passes is not covered), 2 pooling,
  * head mean and histogram, 3 selection (threshold search), 4 compaction and
- * gather. Where one launch takes a layer from the thresholds to the copied rows
- * (only up to 65536 scored tokens, 32768 in ckv_select), stage 3 covers it, stage
- * 4's two events are recorded on the stream right behind it, so every pair is
- * valid after any call and begin[3] to end[4] is selection and gather. Arrays are hipEvent_t[CKV_NUM_STAGES] owned by the caller, created
- * with timing enabled; a NULL entry leaves that stage untimed (each timed
- * launch costs a few microseconds of dispatch overlap); pass NULL arrays to
- * stop. Per host thread. */
+ * gather. Where one launch takes a layer from the thresholds to the copied
+ * rows (only up to 65536 scored tokens, 32768 in ckv_select), stage 3 covers
+ * it and stage 4's two events are recorded on the stream right behind it: every
+ * pair of the stages a call runs is valid after it, and begin[3] to end[4] is
+ * selection and gather. Arrays are hipEvent_t[CKV_NUM_STAGES] owned by the
+ * caller, created with timing enabled; a NULL entry leaves that stage untimed
+ * (each timed launch costs a few microseconds of dispatch overlap); pass NULL
+ * arrays to stop. Per host thread. */
 #define CKV_NUM_STAGES 5
 int ckv_set_stage_events(void *const *begin, void *const *end);
 

@@ -448,8 +448,8 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 // results are added in LDS, and only rows that exist are written out.
 // Shared 64-key blocks behind two barriers, with half the waves idle at up to
 // 32 rows and a 32-row partial per wave, took 122 us + 27 us for the merge on
-// four caches of 8192 to 98304 tokens (402 MB of K and V); this takes 61 + 5 us,
-// 6.5 TB/s.
+// four caches of 8192 to 98304 tokens (403 MB of K and V); this takes 64 + 5 us,
+// 6.3 TB/s.
 template <int DT, int D, int NQ>
 __global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(DT != 2 && NQ == 1 ? 2 : 1)))
 void decode_kernel(const DecodeBatch B) {
@@ -747,7 +747,7 @@ void decode_kernel(const DecodeBatch B) {
 // take every such chunk in turn with U of them in flight, then meet in LDS in a
 // fixed order. One thread per output walking all slots 16 at a time was a
 // chain of up to 16 trips to memory (27 us for four caches of 8192 to 98304
-// tokens, now 4.7 us).
+// tokens, now 4.6 us).
 template <int D>
 __global__ __launch_bounds__(kDecThreads) void decode_merge_kernel(const DecodeBatch B) {
   constexpr int C4 = D / 4, NG = kDecThreads / C4, U = 8;

@@ -16,6 +16,7 @@ int record_hip_error(int hip_status);
 
 
 constexpr int kMaxSeqs = 16;
+static_assert(kMaxSeqs == kPlanSeqs, "the parts of every prompt");
 constexpr int kMaxQHeads = 128;
 constexpr int kMaxKvHeads = 64;
 constexpr int kMaxRows = 128;      // chosen-head rows per group after padding each head to 8
@@ -36,7 +37,7 @@ constexpr int kUnitCopyRows = 512;
 // that one layer's units are split into parts for, with and without copies of
 // the kept rows: every part reads all of a unit's scores (1.6 us per 16384),
 // where the filter, resolve and compact launches share them out. With copies,
-// 8 KV heads: 32768 tokens, 2048 kept: 20 us against 32 us for the three
+// 8 KV heads: 32768 tokens, 2048 kept: 21 us against 32 us for the three
 // launches; 131072 tokens, 1024 kept: 28 against 26 us. Without copies: 65533
 // tokens, 2048 kept: 22 against 20 us.
 constexpr int64_t kUnitTokens = 131072;

@@ -1,5 +1,5 @@
-// Launch plans that are plain arithmetic on sizes: how decode attention is cut
-// into workgroups. No HIP in here, so that the rules can be tested on the host.
+// Launch plans that are plain arithmetic on sizes: how decode attention and one
+// layer's selection are cut into workgroups. No HIP in here, so that the rules can be tested on the host.
 #pragma once
 
 #include <stdint.h>
@@ -105,7 +105,7 @@ struct UnitParts {
 // 256 rows, else half a round. The other half is what a caller's other streams
 // run on meanwhile: layers of 32768 tokens, 2048 kept by each of 8 heads, over
 // four streams took 49.6 us each with a whole round, 43.4 with half, over two
-// 50.7 and 47.6; on one stream 61.0 and 61.4. Short prompts' K passes leave CUs
+// 50.7 and 47.6; on one stream 61.0 and 60.6. Short prompts' K passes leave CUs
 // free by themselves: 4013 tokens on one stream took 42.0 us with a round, 42.7
 // with half. With 32768 of 65000 tokens kept the copies count: 128 and 145 us.
 constexpr int64_t kPartShort = 8192;

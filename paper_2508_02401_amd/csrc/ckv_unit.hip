@@ -494,12 +494,12 @@ __global__ __launch_bounds__(kUT) void select_unit_kernel(const MultiArgs m) {
   unit_body(a, s, u - s * a.n_sg, 0, 1, m.unit_copy != 0, sm);
 }
 
-// One layer: n_parts workgroups per unit. Bound by its chain of dependent steps
-// (a dozen barriers, three trips to memory): 14 us at 1024 tokens, 21.5 us at
+// One layer, the parts of every unit as dealt out. Bound by its chain of dependent
+// steps (a dozen barriers, three trips to memory): 13 us at 1024 tokens, 21 us at
 // 32768 with 2048 rows of 8 heads kept, where filter, resolve and compact took
 // 20 and 32 us. Two prompts of 24571 and 9001 tokens that share one selection
 // for 8 heads had all copies made by the few ranges holding kept tokens: 58
-// us, now 18 us.
+// us, now 17 us.
 __global__ __launch_bounds__(kUT) void select_parts_kernel(const LayerArgs a, const UnitParts p) {
   __shared__ UnitLds sm;
   args_ready(args_touch<sizeof(LayerArgs) + sizeof(UnitParts)>());
